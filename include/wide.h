@@ -120,8 +120,11 @@ wide_status_t wide_mask_reorder(const uint8_t* mask, int64_t M, int32_t n_groups
  *   h_out       optional [M][d_ff] output of the intermediate (inactive
  *               blocks +0); NULL => kept in the workspace.
  *   y           [M][d_model] output.
- *   ws          workspace, >= wide_workspace_size(WIDE_OP_FFN, dt, M, d_model,
- *               d_ff, G) bytes.
+ *   ws          workspace of wide_workspace_size(WIDE_OP_FFN, dt, M, d_model,
+ *               d_ff, G) bytes.  That size includes up to 64 MiB for partial
+ *               sums of the down projection: with less of it the call cuts
+ *               fewer tiles along d_ff, or none (slower; the results differ
+ *               only in fp32 summation order).
  */
 wide_status_t wide_ffn_masked(wide_dtype_t dt, int64_t M, int32_t d_model,
                               int32_t d_ff, int32_t group_size,
@@ -137,8 +140,9 @@ wide_status_t wide_ffn_masked(wide_dtype_t dt, int64_t M, int32_t d_model,
  * harnesses that forbid allocation).  Same arguments, semantics and errors as
  * wide_ffn_masked minus ws/ws_bytes; the scratch it needs (the reorder, H
  * when h_out is NULL, the K-axis scratch) lives in a device array inside the
- * library of wide_static_scratch_bytes() bytes (32 MiB) per GPU, held from the
- * first call on that GPU until the process ends.  A call needing more scratch
+ * library of wide_static_scratch_bytes() bytes (32 MiB) per GPU, and the
+ * partial sums of the down projection in a second one (64 MiB, enough for any
+ * call); both are held until the process ends.  A call needing more scratch
  * than that (wide_workspace_size(WIDE_OP_FFN, ...) > 32 MiB, e.g. a long
  * prefill with h_out NULL) returns WIDE_ERR_WORKSPACE before enqueuing
  * anything.  Nothing is allocated and no library routine that allocates is

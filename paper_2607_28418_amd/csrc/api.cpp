@@ -118,7 +118,37 @@ struct KWS {
   uint8_t* tu = nullptr;
   int32_t* perm = nullptr;  // tokens ordered by mask pattern (dense-masked, few groups)
   int32_t* pat = nullptr;   // scratch of that ordering
+  // What the workspace holds beyond the call's own pieces: partial sums of the
+  // dense-masked schedule's last round (it splits less, or not at all, where
+  // they do not fit).
+  float* part = nullptr;
+  size_t part_floats = 0;
 };
+
+// The dense-masked 256-tile schedule runs this K axis (bf16 prefill).
+bool kaxis_kd256(int K, int N, int G, int path) {
+  return path != 2 && !kaxis_row_gathered(K, N, G) && g_big_tiles && N % wide::kT256 == 0 &&
+         K / G <= wide::kKd256MaxGroups;
+}
+size_t kaxis_part_bytes(int64_t M, int K, int N, int G, int path) {
+  return kaxis_kd256(K, N, G, path) ? wide::kd256_part_floats(M, N, K, K / G) * sizeof(float) : 0;
+}
+// The rest of the workspace (everything else is carved) holds partial sums,
+// unless the call brings `extra` memory for them.
+struct PartMem {
+  float* p = nullptr;
+  size_t floats = 0;
+};
+void take_rest(const Carve& c, size_t ws_bytes, KWS& k, const PartMem& extra = PartMem{}) {
+  if (extra.p) {
+    k.part = extra.p;
+    k.part_floats = extra.floats;
+    return;
+  }
+  if (!c.base || ws_bytes <= c.off) return;
+  k.part = reinterpret_cast<float*>(c.base + c.off);
+  k.part_floats = (ws_bytes - c.off) / sizeof(float);
+}
 
 // The dense-masked 256-tile schedule reads its rows in mask-pattern order
 // when there are few groups (2..8): tiles then skip the groups none of their
@@ -243,6 +273,13 @@ size_t ffn_ws_bytes(wide_dtype_t dt, int64_t M, int D, int Dff, int G, bool need
     carve_kaxis(c, M, D, ng, kpath, k);
   }
   return c.off;
+}
+
+// Partial sums of the down projection's last round, beyond ffn_ws_bytes().
+size_t ffn_part_bytes(wide_dtype_t dt, int64_t M, int D, int Dff, int G) {
+  if (dt != WIDE_BF16 || use_decode(dt, M)) return 0;
+  const bool small = small_groups(dt, G);
+  return kaxis_part_bytes(M, Dff, D, small ? wide::kKMergeWidth : G, small ? 1 : k_path_for(G));
 }
 
 // ---- attention ----------------------------------------------------------------------
@@ -390,7 +427,13 @@ wide_status_t run_kaxis(const uint16_t* a, const uint16_t* w, const uint8_t* mas
     if ((e = wide::launch_f32_to_bf16(kws.acc32, y, M * (int64_t)N, s)) != hipSuccess)
       return hip_fail(e, "f32_to_bf16");
   } else {
-    const bool use256 = big && K / G <= wide::kKd256MaxGroups;
+    const bool use256 = kaxis_kd256(K, N, G, path);
+    if (use256 && kws.part) {
+      const wide::Kd256Tail t = wide::kd256_tail(M, N, K, K / G, kws.part_floats);
+      ka.tail_base = t.base;
+      ka.split = t.split;
+      ka.part = kws.part;
+    }
     if (use256 && kaxis_pattern_order(N, K / G, path) && kws.perm) {
       if ((e = wide::launch_pattern_order(mask, M, K / G, kws.perm, kws.pat, s)) != hipSuccess)
         return hip_fail(e, "pattern order");
@@ -551,7 +594,8 @@ size_t wide_workspace_size(wide_op_t op, wide_dtype_t dt, int64_t M, int32_t d_m
     }
     case WIDE_OP_FFN:
       if (ffn_shape(dt, M, d_model, d_inner, group_size) != WIDE_OK) return SIZE_MAX;
-      return ffn_ws_bytes(dt, M, d_model, d_inner, group_size, true, true, 0);
+      return ffn_ws_bytes(dt, M, d_model, d_inner, group_size, true, true, 0) +
+             ffn_part_bytes(dt, M, d_model, d_inner, group_size);
     case WIDE_OP_ROUTER: {
       if (check_common(dt, M) != WIDE_OK || dt != WIDE_BF16 || d_model <= 0 || d_model % 64 ||
           group_size < 1 || group_size > wide::kRouterMaxRank || d_inner < 1 || d_inner > 4096)
@@ -568,7 +612,10 @@ size_t wide_workspace_size(wide_op_t op, wide_dtype_t dt, int64_t M, int32_t d_m
           d_inner % group_size || d_inner / group_size > 4096)
         return SIZE_MAX;
       AttnDims d{d_model, 0, 0, 0, group_size, d_inner, -1, d_inner / group_size};
-      return attn_ws_bytes(op == WIDE_OP_QKV ? WIDE_PHASE_QKV : WIDE_PHASE_O, dt, M, d, true, 0);
+      size_t n = attn_ws_bytes(op == WIDE_OP_QKV ? WIDE_PHASE_QKV : WIDE_PHASE_O, dt, M, d, true, 0);
+      if (op == WIDE_OP_O && dt == WIDE_BF16 && !use_decode(dt, M))
+        n += kaxis_part_bytes(M, d.Nq, d.D, d.G, k_path_for(d.G));
+      return n;
     }
   }
   return SIZE_MAX;
@@ -640,11 +687,13 @@ wide_status_t wide_router(wide_dtype_t dt, int64_t M, int32_t d_model, int32_t r
   return ok();
 }
 
-wide_status_t wide_ffn_masked(wide_dtype_t dt, int64_t M, int32_t d_model, int32_t d_ff,
-                              int32_t group_size, const uint8_t* mask, const int32_t* idx,
-                              const int32_t* counts, const void* x, const void* w_gate,
-                              const void* w_up, const void* w_down, void* h_out, void* y,
-                              void* ws, size_t ws_bytes, hipStream_t stream) {
+namespace {
+// wide_ffn_masked; `part` (optional) holds the partial sums of the K axis's
+// last round instead of the rest of the workspace.
+wide_status_t ffn_masked(wide_dtype_t dt, int64_t M, int32_t d_model, int32_t d_ff, int32_t group_size,
+                         const uint8_t* mask, const int32_t* idx, const int32_t* counts, const void* x,
+                         const void* w_gate, const void* w_up, const void* w_down, void* h_out, void* y, void* ws,
+                         size_t ws_bytes, const PartMem& part, hipStream_t stream) {
   CHECK(ffn_shape(dt, M, d_model, d_ff, group_size));
   if ((idx == nullptr) != (counts == nullptr))
     return fail(WIDE_ERR_INVALID_ARG, "idx and counts must both be given or both be NULL");
@@ -698,6 +747,7 @@ wide_status_t wide_ffn_masked(wide_dtype_t dt, int64_t M, int32_t d_model, int32
     uint8_t* merged = c.take<uint8_t>((size_t)M * nm);
     KWS kws;
     carve_kaxis(c, M, D, nm, 1, kws);
+    take_rest(c, ws_bytes, kws, part);
     wide::MN256Args ma{};
     ma.x = static_cast<const uint16_t*>(x);
     ma.M = M;
@@ -721,6 +771,7 @@ wide_status_t wide_ffn_masked(wide_dtype_t dt, int64_t M, int32_t d_model, int32
   carve_reorder(c, M, ng, idx == nullptr, r);
   KWS kws;
   carve_kaxis(c, M, D, ng, kpath, kws);
+  take_rest(c, ws_bytes, kws, part);
   const int32_t* ix = idx;
   const int32_t* ct = counts;
   if (!idx) {
@@ -765,32 +816,51 @@ wide_status_t wide_ffn_masked(wide_dtype_t dt, int64_t M, int32_t d_model, int32
                   D, G, kpath, kws, stream));
   return ok();
 }
+}  // namespace
+
+wide_status_t wide_ffn_masked(wide_dtype_t dt, int64_t M, int32_t d_model, int32_t d_ff,
+                              int32_t group_size, const uint8_t* mask, const int32_t* idx,
+                              const int32_t* counts, const void* x, const void* w_gate,
+                              const void* w_up, const void* w_down, void* h_out, void* y,
+                              void* ws, size_t ws_bytes, hipStream_t stream) {
+  return ffn_masked(dt, M, d_model, d_ff, group_size, mask, idx, counts, x, w_gate, w_up, w_down, h_out, y, ws,
+                    ws_bytes, PartMem{}, stream);
+}
 
 // ---- allocation-free FFN ------------------------------------------------------------
 // For callers that cannot allocate (graph capture, serving loops): the
 // workspace of wide_ffn_masked lives in a file-scope device array instead of
-// the caller's buffer.  Host code never uses the array's name as an address
-// (it is a host-side stand-in there): each device's address comes from
+// the caller's buffer, and the partial sums of the K axis's last round in a
+// second one, large enough for any call, so that both entry points split
+// alike.  Host code never uses the arrays' names as addresses (they are
+// host-side stand-ins there): each device's addresses come from
 // hipGetSymbolAddress, looked up once per device with that device current.
 namespace {
 constexpr size_t kStaticScratchBytes = size_t(32) << 20;
 __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+__device__ __align__(256) float scratch_part[wide::kKd256PartMaxFloats];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
-void* g_scratch_dev[kMaxDevices] = {};  // device address of `scratch`, per device
+struct ScratchAddr {
+  void* ws = nullptr;
+  void* part = nullptr;
+};
+ScratchAddr g_scratch_dev[kMaxDevices];
 
-wide_status_t scratch_address(void** out) {
+wide_status_t scratch_address(ScratchAddr* out) {
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
   if (dev < 0 || dev >= kMaxDevices) return fail(WIDE_ERR_UNSUPPORTED, "device ordinal %d out of range", dev);
   std::lock_guard<std::mutex> lk(g_scratch_mu);
-  if (!g_scratch_dev[dev]) {
-    void* p = nullptr;
-    e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+  if (!g_scratch_dev[dev].ws) {
+    ScratchAddr a;
+    e = hipGetSymbolAddress(&a.ws, HIP_SYMBOL(scratch));
     if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
-    if (!p) return fail(WIDE_ERR_HIP, "hipGetSymbolAddress(scratch) returned NULL");
-    g_scratch_dev[dev] = p;
+    e = hipGetSymbolAddress(&a.part, HIP_SYMBOL(scratch_part));
+    if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch_part)");
+    if (!a.ws || !a.part) return fail(WIDE_ERR_HIP, "hipGetSymbolAddress returned NULL");
+    g_scratch_dev[dev] = a;
   }
   *out = g_scratch_dev[dev];
   return WIDE_OK;
@@ -812,12 +882,11 @@ wide_status_t wide_ffn_masked_noalloc(wide_dtype_t dt, int64_t M, int32_t d_mode
     return fail(WIDE_ERR_WORKSPACE,
                 "this call needs %zu bytes of scratch; the static scratch holds %zu (pass h_out, or use "
                 "wide_ffn_masked with a workspace)", need, kStaticScratchBytes);
-  if (M == 0) return wide_ffn_masked(dt, M, d_model, d_ff, group_size, mask, idx, counts, x, w_gate, w_up,
-                                     w_down, h_out, y, nullptr, 0, stream);
-  void* ws = nullptr;
-  if (need) CHECK(scratch_address(&ws));
-  return wide_ffn_masked(dt, M, d_model, d_ff, group_size, mask, idx, counts, x, w_gate, w_up, w_down, h_out, y,
-                         ws, need ? kStaticScratchBytes : 0, stream);
+  ScratchAddr a;
+  if (M > 0 && (need || ffn_part_bytes(dt, M, d_model, d_ff, group_size))) CHECK(scratch_address(&a));
+  return ffn_masked(dt, M, d_model, d_ff, group_size, mask, idx, counts, x, w_gate, w_up, w_down, h_out, y,
+                    need ? a.ws : nullptr, need ? kStaticScratchBytes : 0,
+                    PartMem{static_cast<float*>(a.part), wide::kKd256PartMaxFloats}, stream);
 }
 
 wide_status_t wide_qkvo_masked(wide_phase_t phase, wide_dtype_t dt, int64_t M, int32_t d_model,
@@ -969,6 +1038,7 @@ wide_status_t wide_qkvo_masked(wide_phase_t phase, wide_dtype_t dt, int64_t M, i
   }
   KWS kws;
   carve_kaxis(c, M, d.D, ng, kpath, kws);
+  take_rest(c, ws_bytes, kws);
   CHECK(run_kaxis(x, static_cast<const uint16_t*>(w_o), mask, ix, ct, static_cast<uint16_t*>(y), M, d.Nq, d.D,
                   d.G, kpath, kws, stream));
   return ok();

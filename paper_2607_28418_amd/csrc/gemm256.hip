@@ -543,8 +543,22 @@ __global__ __launch_bounds__(NT) void wide_mn256_tail(MN256Args a) {
 // of each XCD's contiguous range in turn, which needs 18 and, chip-wide,
 // every row panel in each round).  Tiles past the last full round, and
 // shapes the blocks do not fit, keep that m-major walk.
-__device__ __forceinline__ void kd256_coords(int n_tiles, int m_tiles, int& m_tile, int& n_tile) {
-  const int total = m_tiles * n_tiles;
+//
+// The last round.  The tiles past the last full round (every tile, when the
+// launch has fewer than 256) would leave CUs idle for a whole tile's time,
+// and a lone tile is bound by one CU's memory latency: about 1.15 us per
+// 64-deep step however few CUs are busy (32 tiles over K = 14336: 250 us).
+// kd256_tail cuts those tiles along k into `split` chunks, one workgroup
+// each, so that they fill the chip once; every chunk writes fp32 partial sums
+// and wide_kd256_finish adds them in chunk order.  Chunks are fixed ranges of
+// k, not shares of the tile's live groups, so a row's sum does not depend on
+// which other rows share its tile.  Workgroups of one chunk and column tile
+// (all row panels) sit next to each other on one XCD: its L2 reads that
+// slice of the weights once, and with 8 chunks each XCD owns one slice of the
+// activations too.  Llama-3-8B down, kernel plus finish: 300 tokens 253 ->
+// 55 + 9 us, 1000 tokens 274 -> 105 + 14, 2048 tokens 284 -> 190 + 15; at
+// 3000 tokens (192 of 256 tiles) a split would not fill the chip better.
+__device__ __forceinline__ void kd256_coords(int n_tiles, int total, int& m_tile, int& n_tile) {
   const bool blocks = n_tiles % 2 == 0 && n_tiles <= 256 && 256 % n_tiles == 0 && (256 / n_tiles) % 4 == 0;
   const int rounds = blocks ? total / 256 : 0;
   const int id = blockIdx.x;
@@ -587,13 +601,30 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
   KdTables& tb = *reinterpret_cast<KdTables*>(reinterpret_cast<char*>(smem) + (NWR == 0 ? Rg::LDS : 0));
   const uint16_t* zero = g_zero_blk;
   const int n_tiles = a.N / BN;
-  int m_tile, n_tile;
-  kd256_coords(n_tiles, (int)((a.M + BM - 1) / BM), m_tile, n_tile);
+  int m_tile, n_tile, chunk = -1;
+  if ((int)blockIdx.x < a.tail_base) {
+    kd256_coords(n_tiles, a.tail_base, m_tile, n_tile);
+  } else {  // a chunk of a tile of the last round
+    const int rem = (int)((a.M + BM - 1) / BM) * n_tiles - a.tail_base, mt = rem / n_tiles;
+    const int j = xcd_remap(blockIdx.x - a.tail_base, rem * a.split);
+    chunk = j / rem;
+    m_tile = a.tail_base / n_tiles + j % rem % mt;
+    n_tile = j % rem / mt;
+  }
   const int64_t m0 = (int64_t)m_tile * BM;
   const int n0 = n_tile * BN;
   const int ng = a.K / a.G;
   const int nw = (ng + 31) / 32;
   const int tid = threadIdx.x;
+  const int spg = a.G / BK;  // k steps per group
+  // the workgroup's k steps [u0, u1) and the groups [g0, g1) they touch
+  int u0 = 0, u1 = a.K / BK;
+  if (chunk >= 0) {
+    const int u = u1;
+    u0 = u * chunk / a.split;
+    u1 = u * (chunk + 1) / a.split;
+  }
+  const int g0 = u0 / spg, g1 = (u1 + spg - 1) / spg;
 
   if (tid < nw) tb.uni[tid] = 0u;
   __syncthreads();
@@ -605,8 +636,13 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
     const int64_t p = m0 + r;
     const int64_t t = p < a.M ? token(p) : a.M;
     uint32_t bits = 0;
-    if (t < a.M) bits = mask_bits32(a.mask + t * ng + wd * 32, min(32, ng - wd * 32), ng);
+    // (words with no group of the workgroup's range are never used)
+    if (t < a.M && wd * 32 < g1 && wd * 32 + 32 > g0)
+      bits = mask_bits32(a.mask + t * ng + wd * 32, min(32, ng - wd * 32), ng);
     tb.mbits[r][wd] = bits;
+    const int lo = max(g0 - wd * 32, 0), hi = min(g1 - wd * 32, 32);
+    if (lo > 0) bits &= ~0u << min(lo, 31);
+    if (hi < 32) bits &= hi > 0 ? ~0u >> (32 - hi) : 0u;
     if (bits) atomicOr(&tb.uni[wd], bits);
   }
   __syncthreads();
@@ -624,8 +660,16 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
     }
   }
   __syncthreads();
-  const int spg = a.G / BK;  // k steps per group
-  const int nsteps = __builtin_amdgcn_readfirstlane(tb.n_live) * spg;
+  // Steps run over the live groups; a chunk that starts or ends inside a
+  // group takes that group's part only.
+  const int n_live = __builtin_amdgcn_readfirstlane(tb.n_live);
+  int sbeg = 0, nsteps = n_live * spg;
+  if (n_live > 0) {
+    const int gf = __builtin_amdgcn_readfirstlane((int)tb.groups[0]);
+    const int gl = __builtin_amdgcn_readfirstlane((int)tb.groups[n_live - 1]);
+    sbeg = max(0, u0 - gf * spg);
+    nsteps -= sbeg + max(0, (gl + 1) * spg - u1);
+  }
 
   int srow[S];
   const uint16_t* wpanel = uniform_ptr(a.w + (int64_t)n0 * a.K);
@@ -686,6 +730,7 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
   };
   const int lg = __builtin_ctz(a.G), lsp = lg - 6;  // G is a power of two, at least BK
   auto koff = [&](int s) {
+    s += sbeg;
     const int gi = s >> lsp;
     return group(gi) * a.G + (s & (spg - 1)) * BK;
   };
@@ -716,8 +761,22 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
   if (tid < BM && m0 + tid < a.M) my_row = (int)token(m0 + tid);
   run_tile<Rg, 0>(smem, nsteps, koff, lda, ldb, bb, a.M - m0, acc);
 
-  const int* map = stage_row_map(smem, my_row);
   const int col = acc_col();
+  if (chunk >= 0) {  // fp32 partial sums, rows in tile order
+    const int64_t p0 = (int64_t)(a.tail_base / n_tiles) * BM, rows = a.M - p0;
+    float* P = a.part + ((int64_t)chunk * rows + (m0 - p0)) * a.N + n0 + col;
+#pragma unroll
+    for (int fm = 0; fm < 4; ++fm)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = acc_row(fm, i);
+        if (m0 + r >= a.M) continue;
+#pragma unroll
+        for (int fn = 0; fn < 4; ++fn) P[(int64_t)r * a.N + bb[fn]] = acc[fm][fn][i];
+      }
+    return;
+  }
+  const int* map = stage_row_map(smem, my_row);
 #pragma unroll
   for (int fm = 0; fm < 4; ++fm)
 #pragma unroll
@@ -728,6 +787,21 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
 #pragma unroll
       for (int fn = 0; fn < 4; ++fn) o[bb[fn]] = f32_to_bf16_hw(acc[fm][fn][i]);
     }
+}
+
+// y rows [m0, M) (through the pattern order) = the chunks' partial sums added
+// in chunk order; four columns per thread.
+__global__ __launch_bounds__(NT) void wide_kd256_finish(const float* __restrict__ part, int split, int64_t m0,
+                                                        int64_t rows, int N, const int32_t* __restrict__ perm,
+                                                        uint16_t* __restrict__ y) {
+  const int64_t n = rows * N, i = ((int64_t)blockIdx.x * NT + threadIdx.x) * 4;
+  if (i >= n) return;
+  f32x4 s = *reinterpret_cast<const f32x4*>(part + i);
+#pragma unroll 8
+  for (int q = 1; q < split; ++q) s += *reinterpret_cast<const f32x4*>(part + q * n + i);
+  const int64_t p = m0 + i / N;
+  const int64_t t = perm ? (int64_t)perm[p] : p;
+  *reinterpret_cast<uint2*>(y + t * N + i % N) = uint2{pack_bf16x2_hw(s[0], s[1]), pack_bf16x2_hw(s[2], s[3])};
 }
 
 // -------------------------------------------------------------- K-axis, scatter
@@ -887,10 +961,41 @@ bool mn256_tail_ok(const MN256Args& a, int bno) {
   return true;
 }
 
-hipError_t launch_kd256(const KArgs& a, hipStream_t s) {
+// Chunks of the last round: as many as fill the 256 CUs once, each at least
+// kKdMinSteps deep.
+constexpr int kKdMaxSplit = 16, kKdMinSteps = 4;
+Kd256Tail kd256_tail(int64_t M, int N, int K, int ng, size_t avail) {
+  const int n_tiles = N / BN;
+  const int64_t m_tiles = (M + BM - 1) / BM, total = m_tiles * n_tiles;
+  Kd256Tail t{(int)total, 1, M};
+  if (total == 0 || n_tiles > 256) return t;
+  const int mr = 256 / n_tiles;  // m-tiles of a full round
+  const int64_t mb = m_tiles / mr * mr, rem = total - mb * n_tiles, rows = M - mb * BM;
+  // (rows the mask-pattern order may move between a whole and a split tile
+  // keep one summation order: there only launches of less than a round split)
+  if (rem == 0 || (mb > 0 && ng > 1 && ng <= kPatternMaxGroups)) return t;
+  int64_t split = 256 / rem;
+  if (split > kKdMaxSplit) split = kKdMaxSplit;
+  if (split > K / BK / kKdMinSteps) split = K / BK / kKdMinSteps;
+  if (split > (int64_t)(avail / ((size_t)rows * N))) split = (int64_t)(avail / ((size_t)rows * N));
+  if (split >= 2) t = Kd256Tail{(int)(mb * n_tiles), (int)split, mb * BM};
+  return t;
+}
+size_t kd256_part_floats(int64_t M, int N, int K, int ng) {
+  const Kd256Tail t = kd256_tail(M, N, K, ng, SIZE_MAX);
+  return t.split > 1 ? (size_t)t.split * (size_t)(M - t.m0) * (size_t)N : 0;
+}
+
+hipError_t launch_kd256(const KArgs& args, hipStream_t s) {
+  KArgs a = args;
   const int64_t m_tiles = (a.M + BM - 1) / BM;
-  const int64_t total = m_tiles * (a.N / BN);
-  if (total == 0) return hipSuccess;
+  const int64_t tiles = m_tiles * (a.N / BN);
+  if (tiles == 0) return hipSuccess;
+  if (a.split < 2) {
+    a.tail_base = (int)tiles;
+    a.split = 1;
+  }
+  const int64_t total = a.tail_base + (tiles - a.tail_base) * a.split;
   if (a.K / a.G > kKd256MaxGroups) return hipErrorInvalidValue;
   const int ng = a.K / a.G;
   const bool buf = views_fit(a.M, a.K);
@@ -906,6 +1011,11 @@ hipError_t launch_kd256(const KArgs& a, hipStream_t s) {
     WIDE_RING_LAUNCH("wide_kd256<0>", (wide_kd256<0, 64, true>), kd256_lds<0>(), (unsigned)total, s, a);
   else
     WIDE_RING_LAUNCH("wide_kd256<0>", (wide_kd256<0, 64, false>), kd256_lds<0>(), (unsigned)total, s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.split < 2) return e;
+  const int64_t p0 = (int64_t)(a.tail_base / (a.N / BN)) * BM, rows = a.M - p0;
+  WIDE_LAUNCH(wide_kd256_finish, dim3((unsigned)((rows * a.N / 4 + NT - 1) / NT)), dim3(NT), 0, s, a.part, a.split,
+              p0, rows, a.N, a.perm, a.y);
   return hipGetLastError();
 }
 

@@ -70,6 +70,10 @@ struct KArgs {
   int64_t M;
   int K, N, G;
   int pack;            // 256-tile scatter: K-groups run in turn by one workgroup (>= 1)
+  // 256-tile dense-masked: tiles [tail_base, total) are cut along k into
+  // `split` chunks (kd256_tail); part: [split][M - tail_m0][N] fp32.
+  int tail_base, split;
+  float* part;
 };
 
 constexpr int kKTileM = 128;
@@ -130,6 +134,16 @@ bool mn256_tail_ok(const MN256Args& a, int bno);
 
 constexpr int kT256 = 256;
 hipError_t launch_mn256(const MN256Args& a, bool swiglu, hipStream_t s);
+// The last, partial round of a dense-masked launch (see gemm256.hip): tiles
+// [base, total) are each run by `split` workgroups (1: not split), token rows
+// from m0 on; at most `avail` floats of partial sums.
+struct Kd256Tail {
+  int base, split;
+  int64_t m0;
+};
+Kd256Tail kd256_tail(int64_t M, int N, int K, int ng, size_t avail);
+size_t kd256_part_floats(int64_t M, int N, int K, int ng);
+constexpr size_t kKd256PartMaxFloats = (size_t)256 * 256 * 256;  // at most 256 chunks of one tile's sums
 hipError_t launch_kd256(const KArgs& a, hipStream_t s);
 hipError_t launch_ks256(const KArgs& a, hipStream_t s);
 constexpr int kKd256MaxGroups = 512;

@@ -648,3 +648,34 @@ def test_qkv_tail_split_matches(orc, M, order):
         W.wide_set_option("mn_tail", tail)
         check_qkvo(orc, c, kpath=0)
     W.wide_set_option("mn_tail", 1)
+
+
+@pytest.mark.parametrize("M,D,n_q,G,chunks", [
+    (65, 4096, 8, 512, None),     # one m-tile, chunks that end inside a group
+    (257, 512, 16, 128, None),    # one row in the last m-tile
+    (700, 768, 12, 512, None),    # column tiles that do not divide a round
+    (700, 768, 12, 512, 2.5),     # room for two chunks
+    (700, 768, 12, 512, 1.5),     # no room: not split
+    (4100, 4096, 12, 128, None),  # a full round, then a split one of four rows
+    (2100, 4096, 8, 128, None),   # more than half a round: not split
+])
+def test_kaxis_last_round_split(orc, M, D, n_q, G, chunks):
+    """The dense-masked K axis cuts the tiles past its last full round of 256
+    along k; the pattern order stays bitwise neutral, and with a workspace
+    that holds fewer partial sums it splits less or not at all."""
+    say("kaxis last round", M, D, n_q, G, chunks)
+    W.wide_set_option("k_path", 1)
+    c = synth.attn_case(M + G, M, D, n_q, n_q, 128, G, mask="bernoulli")
+    d = attn_dev(c)
+    n = W.wide_workspace_size(W.OP_O, W.BF16, M, D, n_q * 128, G)
+    if chunks is not None:
+        n = min(n, 65536 + int(chunks * M * D * 4))   # (the other pieces take less than 64 KiB)
+    outs = []
+    for pattern in (1, 0):
+        W.wide_set_option("kd_pattern", pattern)
+        ws = torch.full((n,), 0x5A, dtype=torch.uint8, device=dev())
+        outs.append(W.wide_qkvo_masked(W.PHASE_O, d["a"], d["mask"], G, n_q, n_q, 128, w_o=d["w_o"], ws=ws))
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+    rows = np.unique(np.r_[0, 1, 255, 256, M - 1, M - 2, synth.rng(M).choice(M, 40)])
+    check_kproj(orc, c.a, c.w_o, c.mask, G, outs[0], rows=rows[rows < M], what="o")
