@@ -125,9 +125,11 @@ struct KWS {
   size_t part_floats = 0;
 };
 
-// The dense-masked 256-tile schedule runs this K axis (bf16 prefill).
+// The dense-masked 256-tile schedule runs this K axis (bf16 prefill).  Its
+// step -> group map is a shift, so head groups whose width is not a power of
+// two (three heads of 128, say) take the 128-tile kernel.
 bool kaxis_kd256(int K, int N, int G, int path) {
-  return path != 2 && !kaxis_row_gathered(K, N, G) && g_big_tiles && N % wide::kT256 == 0 &&
+  return path != 2 && !kaxis_row_gathered(K, N, G) && g_big_tiles && N % wide::kT256 == 0 && is_pow2(G) &&
          K / G <= wide::kKd256MaxGroups;
 }
 size_t kaxis_part_bytes(int64_t M, int K, int N, int G, int path) {

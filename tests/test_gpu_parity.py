@@ -679,3 +679,15 @@ def test_kaxis_last_round_split(orc, M, D, n_q, G, chunks):
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
     rows = np.unique(np.r_[0, 1, 255, 256, M - 1, M - 2, synth.rng(M).choice(M, 40)])
     check_kproj(orc, c.a, c.w_o, c.mask, G, outs[0], rows=rows[rows < M], what="o")
+
+
+@pytest.mark.parametrize("M,n_q,G", [(300, 6, 384), (130, 10, 640)])
+def test_o_group_width_not_a_power_of_two(orc, M, n_q, G):
+    """Head groups of three or five 128-wide heads: the 256-tile K axis maps
+    steps to groups by shifts, so these run on the 128 tiles."""
+    say("o group width", M, n_q, G)
+    c = synth.attn_case(M + G, M, 256, n_q, n_q // 2, 128, G, mask="bernoulli")
+    d = attn_dev(c)
+    y = W.wide_qkvo_masked(W.PHASE_O, d["a"], d["mask"], G, n_q, n_q // 2, 128, w_o=d["w_o"])
+    torch.cuda.synchronize()
+    check_kproj(orc, c.a, c.w_o, c.mask, G, y, what="o")
