@@ -1,16 +1,28 @@
-// fp32 masked projections (vector ALU, no reduced-precision matrix ops).
+// fp32 masked projections on the fp32 matrix cores (no reduced precision).
 //
-// The fp32 data path keeps every value in fp32 end to end.  Both kernels use
-// a 16 x 16 output tile per 256-thread workgroup with 64-wide k slices staged
-// in LDS.
+// The fp32 data path keeps every value in fp32 end to end.
 //   f32_nproj  out[t, n] = x_t . w[n] for active (t, group of n), else +0
 //              (optionally the SwiGLU pair: silu(x_t . w0[n]) * (x_t . w1[n]));
-//              a tile whose 16 tokens are all inactive in its group exits
-//              after writing +0.  (WIDE Section 3.1, equations (1) and (3).)
+//              a tile whose tokens are all inactive in its groups exits after
+//              writing +0.  (WIDE Section 3.1, equations (1) and (3).)
 //   f32_kproj  y[t, n] = sum over active groups g of t of
 //              sum_{k in g} a[t, k] w[n, k]; inactive (t, g) blocks are not
-//              read (zero in LDS).  (Section 3.1 equations (2)-(3), the
-//              GEMM-K sum of Appendix B.)
+//              read.  (Section 3.1 equations (2)-(3), the GEMM-K sum of
+//              Appendix B.)
+//
+// A workgroup owns a tile of 16*F tokens x 16*F columns (F 1 or 2) and its 8
+// waves share the reduction: each takes a contiguous run of the 16-deep k
+// chunks, loads them straight into MFMA operands (lane l: row l % 16, four
+// consecutive k from 4 * (l / 16); MFMA e of a chunk multiplies element e of
+// the four, the same k on both sides) several chunks ahead, and the waves'
+// partial tiles are added in LDS in wave order.  These calls are small (a
+// 128-token, 512 x 1536 FFN is 0.3 GFLOP), so what bounds them is latency:
+// the wave split shortens the serial chain by 8, nothing in the k loop waits
+// on a barrier, and F is 2 only where enough tiles of 32 remain (frags()).  Against the
+// vector-ALU kernels this replaces (16 x 16 tiles staged through LDS, one
+// serial k loop per workgroup): 128 tokens, d_model 512, d_ff 1536 in groups
+// of 64, gate/up 45 -> 14 us, down 75 -> 10 us; 512 tokens, 1024 x 2048:
+// 240 -> 69 and 168 -> 33 us.
 #include "common.h"
 #include "kernels.h"
 #include "launch.h"
@@ -18,91 +30,242 @@
 namespace wide {
 
 namespace {
-constexpr int T = 16, KS = 64;
+
+constexpr int T = 16, KC = 16, NW = 8, NT = NW * kWave;
+
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-template <bool SWIGLU>
-__global__ __launch_bounds__(256) void wide_f32_nproj(F32NArgs a) {
-  __shared__ float xs[T][KS + 1];
-  __shared__ float w0s[T][KS + 1];
-  __shared__ float w1s[SWIGLU ? T : 1][KS + 1];
-  const int m_tiles = (int)((a.M + T - 1) / T);
-  const int mt = blockIdx.x % m_tiles, nt = blockIdx.x / m_tiles;
-  const int64_t t0 = (int64_t)mt * T;
-  const int n0 = nt * T;
-  const int tid = threadIdx.x, ti = tid / T, ni = tid % T;
-  const int64_t t = t0 + ti;
-  const int g = n0 / a.G;
-  const bool on = t < a.M && (!a.mask || a.mask[t * a.n_groups + g] != 0);
-  if (!__syncthreads_or(on)) {
-    if (t < a.M) a.out[t * a.ldo + n0 + ni] = 0.f;
+// Workgroup id -> tile id: each XCD (workgroups are dealt round-robin to the
+// 8 XCDs) walks a contiguous range of tiles, so the tiles of one column run
+// share its weight rows in that XCD's L2.
+__device__ __forceinline__ int xcd_remap(int id, int n) {
+  const int q = n / 8, r = n % 8;
+  const int xcd = id % 8, local = id / 8;
+  return (xcd < r) ? xcd * (q + 1) + local : r * (q + 1) + (xcd - r) * q + local;
+}
+
+// Wave w's run [c0, c1) of n chunks.
+__device__ __forceinline__ void wave_run(int n, int& c0, int& c1) {
+  const int w = wave_id();
+  c0 = (int)((int64_t)n * w / NW);
+  c1 = (int)((int64_t)n * (w + 1) / NW);
+}
+
+// acc[v][i][j] += A fragment i x B fragment j of weight v over chunks
+// [c0, c1), D chunks in flight.  aoff(c, i): byte offset of the lane's 16
+// bytes of A fragment i at chunk c (called once per chunk, in order);
+// fragments past the views' ends read zeros.
+template <int NV, int F, int D, class AOff>
+__device__ __forceinline__ void k_loop(bufview_t av, const bufview_t (&wv)[NV], uint32_t row_bytes, int c0, int c1,
+                                       AOff aoff, f32x4 (&acc)[NV][F][F]) {
+  const int lane = lane_id();
+  const uint32_t woff = (uint32_t)(lane & 15) * row_bytes + (lane >> 4) * 16;
+  struct Regs {
+    u32x4 a[F], w[NV][F];
+  };
+  auto load = [&](int c, Regs& r) {
+#pragma unroll
+    for (int i = 0; i < F; ++i) r.a[i] = buf_ld16(av, aoff(c, i));
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int j = 0; j < F; ++j)
+        r.w[v][j] = buf_ld16s(wv[v], woff, (uint32_t)j * T * row_bytes + (uint32_t)c * (KC * 4));
+  };
+  auto mma = [&](const Regs& r) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+          for (int j = 0; j < F; ++j)
+            acc[v][i][j] = mfma_f32(__uint_as_float(r.a[i][e]), __uint_as_float(r.w[v][j][e]), acc[v][i][j]);
+  };
+  Regs rr[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (c0 + d < c1) load(c0 + d, rr[d]);
+  for (int c = c0; c < c1; c += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      if (c + d < c1) {
+        mma(rr[d]);
+        if (c + d + D < c1) load(c + d + D, rr[d]);
+      }
+    }
+  }
+}
+
+// The 8 waves' partial tiles added in wave order; out(row, col, sums) runs
+// for every element of the tile.
+template <int NV, int F, class Out>
+__device__ __forceinline__ void reduce_tile(f32x4 (*red)[NW][kWave], const f32x4 (&acc)[NV][F][F], Out out) {
+  const int w = wave_id(), lane = lane_id();
+#pragma unroll
+  for (int v = 0; v < NV; ++v)
+#pragma unroll
+    for (int i = 0; i < F; ++i)
+#pragma unroll
+      for (int j = 0; j < F; ++j) red[(v * F + i) * F + j][w][lane] = acc[v][i][j];
+  __syncthreads();
+  // Thread -> (fragment, accumulator element i, lane): 16 lanes share a row.
+  for (int q = threadIdx.x; q < F * F * 4 * kWave; q += NT) {
+    const int f = q / (4 * kWave), l = q % kWave, e = (q / kWave) % 4;
+    float s[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      s[v] = 0.f;
+#pragma unroll
+      for (int p = 0; p < NW; ++p) s[v] += red[v * F * F + f][p][l][e];
+    }
+    out(f / F * T + (l >> 4) * 4 + e, f % F * T + (l & 15), s);
+  }
+}
+
+}  // namespace
+
+template <bool SWIGLU, int F>
+__global__ __launch_bounds__(NT) void wide_f32_nproj(F32NArgs a) {
+  constexpr int NV = SWIGLU ? 2 : 1, TM = T * F;
+  __shared__ f32x4 red[NV * F * F][NW][kWave];
+  __shared__ uint8_t s_on[TM][F];  // row r runs the group of column fragment j
+  __shared__ int any;
+  const int m_tiles = (int)((a.M + TM - 1) / TM);
+  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int64_t t0 = (int64_t)(tile % m_tiles) * TM;
+  const int n0 = tile / m_tiles * TM;
+  const int rows = (int)min((int64_t)TM, a.M - t0), cols = min(TM, a.N - n0);
+  const int tid = threadIdx.x;
+  if (tid == 0) any = a.mask == nullptr;
+  __syncthreads();
+  if (a.mask && tid < TM * F) {
+    const int r = tid / F, j = tid % F;
+    // (a fragment of 16 columns lies inside one group)
+    const bool on = r < rows && j * T < cols && a.mask[(t0 + r) * a.n_groups + (n0 + j * T) / a.G] != 0;
+    s_on[r][j] = on;
+    if (on) any = 1;
+  }
+  __syncthreads();
+  if (!any) {
+    for (int q = tid; q < rows * cols; q += NT) a.out[(t0 + q / cols) * a.ldo + n0 + q % cols] = 0.f;
     return;
   }
-  float s0 = 0.f, s1 = 0.f;
-  for (int k0 = 0; k0 < a.K; k0 += KS) {
-    for (int i = tid; i < T * KS; i += 256) {
-      const int r = i / KS, c = i % KS, k = k0 + c;
-      const int64_t tr = t0 + r;
-      xs[r][c] = (tr < a.M && k < a.K) ? a.x[tr * a.K + k] : 0.f;
-      w0s[r][c] = (k < a.K) ? a.w0[(int64_t)(n0 + r) * a.K + k] : 0.f;
-      if (SWIGLU) w1s[r][c] = (k < a.K) ? a.w1[(int64_t)(n0 + r) * a.K + k] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int c = 0; c < KS; ++c) {
-      s0 = fmaf(xs[ti][c], w0s[ni][c], s0);
-      if (SWIGLU) s1 = fmaf(xs[ti][c], w1s[ni][c], s1);
-    }
-    __syncthreads();
-  }
-  if (t < a.M) {
-    const float o = on ? (SWIGLU ? silu(s0) * s1 : s0) : 0.f;
-    a.out[t * a.ldo + n0 + ni] = o;
-  }
+  const uint32_t rb = (uint32_t)a.K * 4u;
+  const bufview_t av = buf_view(a.x + t0 * a.K, (uint32_t)rows * rb);
+  bufview_t wv[NV];
+  wv[0] = buf_view(a.w0 + (int64_t)n0 * a.K, (uint32_t)cols * rb);
+  if (SWIGLU) wv[NV - 1] = buf_view(a.w1 + (int64_t)n0 * a.K, (uint32_t)cols * rb);
+  f32x4 acc[NV][F][F];
+#pragma unroll
+  for (int v = 0; v < NV; ++v)
+#pragma unroll
+    for (int i = 0; i < F; ++i)
+#pragma unroll
+      for (int j = 0; j < F; ++j) acc[v][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  int c0, c1;
+  wave_run(a.K / KC, c0, c1);
+  const int lane = lane_id();
+  const uint32_t aoff = (uint32_t)(lane & 15) * rb + (lane >> 4) * 16;
+  k_loop<NV, F, 4>(av, wv, rb, c0, c1, [&](int c, int i) { return aoff + (uint32_t)i * T * rb + (uint32_t)c * (KC * 4); },
+                   acc);
+  reduce_tile<NV, F>(red, acc, [&](int r, int c, const float (&s)[NV]) {
+    if (r >= rows || c >= cols) return;
+    const bool on = !a.mask || s_on[r][c / T];
+    a.out[(t0 + r) * a.ldo + n0 + c] = on ? (SWIGLU ? silu(s[0]) * s[NV - 1] : s[0]) : 0.f;
+  });
 }
 
-__global__ __launch_bounds__(256) void wide_f32_kproj(F32KArgs a) {
-  __shared__ float as[T][KS + 1];
-  __shared__ float ws[T][KS + 1];
-  const int m_tiles = (int)((a.M + T - 1) / T);
-  const int mt = blockIdx.x % m_tiles, nt = blockIdx.x / m_tiles;
-  const int64_t t0 = (int64_t)mt * T;
-  const int n0 = nt * T;
-  const int tid = threadIdx.x, ti = tid / T, ni = tid % T;
-  float s = 0.f;
-  for (int k0 = 0; k0 < a.K; k0 += KS) {
-    for (int i = tid; i < T * KS; i += 256) {
-      const int r = i / KS, c = i % KS, k = k0 + c;
-      const int64_t tr = t0 + r;
-      const bool on = tr < a.M && k < a.K && a.mask[tr * a.n_groups + k / a.G] != 0;
-      as[r][c] = on ? a.a[tr * a.K + k] : 0.f;
-      ws[r][c] = (k < a.K) ? a.w[(int64_t)(n0 + r) * a.K + k] : 0.f;
+template <int F>
+__global__ __launch_bounds__(NT) void wide_f32_kproj(F32KArgs a) {
+  constexpr int TM = T * F, MAXG = 4096;
+  __shared__ f32x4 red[F * F][NW][kWave];
+  __shared__ uint64_t s_bits[TM][MAXG / 64];  // bit g: row r runs group g
+  const int m_tiles = (int)((a.M + TM - 1) / TM);
+  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int64_t t0 = (int64_t)(tile % m_tiles) * TM;
+  const int n0 = tile / m_tiles * TM;
+  const int rows = (int)min((int64_t)TM, a.M - t0), cols = min(TM, a.N - n0);
+  const int w = wave_id(), lane = lane_id(), ng = a.n_groups;
+  for (int s = 0; s * 64 < ng; ++s) {
+    uint8_t m[TM / NW];
+#pragma unroll
+    for (int i = 0; i < TM / NW; ++i) {  // independent loads
+      const int r = i * NW + w, g = s * 64 + lane;
+      m[i] = a.mask[(t0 + min(r, rows - 1)) * ng + min(g, ng - 1)];
     }
-    __syncthreads();
-#pragma unroll 8
-    for (int c = 0; c < KS; ++c) s = fmaf(as[ti][c], ws[ni][c], s);
-    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TM / NW; ++i) {
+      const int r = i * NW + w;
+      const uint64_t b = __ballot(m[i] != 0 && r < rows && s * 64 + lane < ng);
+      if (lane == 0) s_bits[r][s] = b;
+    }
   }
-  const int64_t t = t0 + ti;
-  if (t < a.M) a.y[t * a.N + n0 + ni] = s;
+  __syncthreads();
+  const uint32_t rb = (uint32_t)a.K * 4u;
+  const bufview_t av = buf_view(a.a + t0 * a.K, (uint32_t)rows * rb);
+  const bufview_t wv[1] = {buf_view(a.w + (int64_t)n0 * a.K, (uint32_t)cols * rb)};
+  f32x4 acc[1][F][F];
+#pragma unroll
+  for (int i = 0; i < F; ++i)
+#pragma unroll
+    for (int j = 0; j < F; ++j) acc[0][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  int c0, c1;
+  wave_run(a.K / KC, c0, c1);
+  const uint32_t aoff = (uint32_t)(lane & 15) * rb + (lane >> 4) * 16;
+  // a chunk lies inside one group; the chunks are asked for in order
+  int g = c0 * KC / a.G, left = (g + 1) * a.G - c0 * KC;
+  k_loop<1, F, 4>(av, wv, rb, c0, c1, [&](int c, int i) {
+    const bool on = (s_bits[i * T + (lane & 15)][g >> 6] >> (g & 63)) & 1u;
+    if (i == F - 1 && (left -= KC) == 0) {
+      ++g;
+      left = a.G;
+    }
+    return on ? aoff + (uint32_t)i * T * rb + (uint32_t)c * (KC * 4) : kOffNone;
+  }, acc);
+  reduce_tile<1, F>(red, acc, [&](int r, int c, const float (&s)[1]) {
+    if (r < rows && c < cols) a.y[(t0 + r) * a.N + n0 + c] = s[0];
+  });
 }
+
+namespace {
+// 32 x 32 tiles read half the operand bytes per product of 16 x 16 ones but
+// leave fewer workgroups: taken where they give every CU one, for gate/up
+// (two products per tile) every second CU.  At 192 tiles of 32 (128 tokens, 512 x
+// 1536) gate/up ran 14.0 us with them and 15.7 without; at 128 tiles (256
+// tokens, 512 outputs) down ran 12.8 and 11.0 us.
+int64_t tiles(int64_t M, int N, int tm) { return (M + tm - 1) / tm * ((N + tm - 1) / tm); }
+int frags(int64_t M, int N, bool pair) { return tiles(M, N, 2 * T) >= (pair ? 128 : 256) ? 2 : 1; }
+}  // namespace
 
 hipError_t launch_f32_nproj(const F32NArgs& a, bool swiglu, hipStream_t s) {
-  const int64_t m_tiles = (a.M + T - 1) / T;
-  const int64_t total = m_tiles * (a.N / T);
+  const int f = frags(a.M, a.N, swiglu);
+  const int64_t total = tiles(a.M, a.N, f * T);
   if (total == 0) return hipSuccess;
-  if (swiglu)
-    WIDE_LAUNCH((wide_f32_nproj<true>), dim3((unsigned)total), dim3(256), 0, s, a);
+  const dim3 grid((unsigned)total), block(NT);
+  if (swiglu && f == 2)
+    WIDE_LAUNCH((wide_f32_nproj<true, 2>), grid, block, 0, s, a);
+  else if (swiglu)
+    WIDE_LAUNCH((wide_f32_nproj<true, 1>), grid, block, 0, s, a);
+  else if (f == 2)
+    WIDE_LAUNCH((wide_f32_nproj<false, 2>), grid, block, 0, s, a);
   else
-    WIDE_LAUNCH((wide_f32_nproj<false>), dim3((unsigned)total), dim3(256), 0, s, a);
+    WIDE_LAUNCH((wide_f32_nproj<false, 1>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_f32_kproj(const F32KArgs& a, hipStream_t s) {
-  const int64_t m_tiles = (a.M + T - 1) / T;
-  const int64_t total = m_tiles * (a.N / T);
+  const int f = frags(a.M, a.N, false);
+  const int64_t total = tiles(a.M, a.N, f * T);
   if (total == 0) return hipSuccess;
-  WIDE_LAUNCH(wide_f32_kproj, dim3((unsigned)total), dim3(256), 0, s, a);
+  const dim3 grid((unsigned)total), block(NT);
+  if (f == 2)
+    WIDE_LAUNCH((wide_f32_kproj<2>), grid, block, 0, s, a);
+  else
+    WIDE_LAUNCH((wide_f32_kproj<1>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 

@@ -691,3 +691,27 @@ def test_o_group_width_not_a_power_of_two(orc, M, n_q, G):
     y = W.wide_qkvo_masked(W.PHASE_O, d["a"], d["mask"], G, n_q, n_q // 2, 128, w_o=d["w_o"])
     torch.cuda.synchronize()
     check_kproj(orc, c.a, c.w_o, c.mask, G, y, what="o")
+
+
+@pytest.mark.parametrize("M,D,Dff,G", [
+    (1, 16, 16, 16),          # one chunk: seven of eight waves have none
+    (17, 48, 112, 16),        # one row in the last tile, uneven wave runs
+    (520, 528, 1040, 16),     # 32-wide tiles with half column tiles, two groups per tile
+    (33, 64, 4112, 16),       # more than 64 groups per mask word
+])
+def test_fp32_tiles(orc, M, D, Dff, G):
+    """Edges of the fp32 matrix-core tiles: ragged rows and columns, K runs
+    that do not divide among the waves, inactive input blocks holding NaN."""
+    say("fp32 tiles", M, D, Dff, G)
+    c = synth.ffn_case(M + Dff, M, D, Dff, G, dtype="f32", mask="bernoulli")
+    x, wg, wu, wd, m = ffn_dev(c)
+    h = torch.full((M, Dff), 7.0, device=dev())
+    y = W.wide_ffn_masked(x, wg, wu, wd, m, G, h_out=h)
+    # the K axis alone, through the O projection, on rows whose inactive blocks are poisoned
+    a = torch.where(m.bool().repeat_interleave(G, dim=1), h, torch.nan)
+    o = W.wide_qkvo_masked(W.PHASE_O, a, m, G, Dff // 16, Dff // 16, 16, w_o=wd)
+    torch.cuda.synchronize()
+    rh, ry = orc.ffn(c.x, c.w_gate, c.w_up, c.w_down, c.mask, G)
+    assert_close(h, rh, kind="f32", what="h")
+    assert_close(y, ry, kind="f32", what="y")
+    assert torch.equal(y, o)
