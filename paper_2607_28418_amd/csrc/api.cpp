@@ -1311,6 +1311,14 @@ wide_status_t wide_attention_decode(wide_dtype_t dt, int64_t batch, int32_t L, i
   a.mask = mask;
   a.kv_len = kv_len;
   a.part = static_cast<float*>(ws);
+  // The balanced split keeps its table in front of the segments' partials.
+  a.waves = wide::attn_decode_waves(batch, n_kv_heads, L);
+  const size_t pairs = (size_t)batch * n_kv_heads, table = align_up(pairs * 2 * sizeof(int32_t));
+  const size_t part = (a.waves + pairs) * (size_t)s.qpk * (wide::kAttnHeadDim + 2) * sizeof(float);
+  if (a.waves && table + part <= attention_decode_ws(batch, L, n_q_heads, n_kv_heads)) {
+    a.table = static_cast<int32_t*>(ws);
+    a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + table);
+  }
   a.B = (int)batch;
   a.L = L;
   a.n_q = n_q_heads;

@@ -271,13 +271,17 @@ struct AttnDecArgs {
   uint16_t* o;              // [B][n_q*128] bf16 out
   const uint8_t* mask;      // [B][ng]
   const int32_t* kv_len;    // optional [B]: keys [0, kv_len[b]) are attended (NULL: L)
-  float* part;              // workspace [B][n_q][n_chunks][2 + 128]
+  float* part;              // workspace [slots][qpk][2 + 128]: a slot is (pair, chunk) or a balanced segment
+  int32_t* table;           // balanced split: workspace [B * n_kv][2] = first slot, segments; NULL: equal chunks
+  int waves;                // balanced split: waves sharing the work
   int B, L, n_q, n_kv, ng, hpg, qpk;
   int head_major;           // cache layout (see k)
   int chunk, n_chunks;      // keys per workgroup (multiple of 64), ceil(L / chunk)
   float scale_log2;
 };
 int attn_decode_chunk(int B, int n_kv, int L);
+constexpr int kAttnDecMaxPairs = 2016, kAttnDecWaves = 2048;
+int attn_decode_waves(int64_t B, int n_kv, int L);  // 0: no balanced split for this shape
 hipError_t launch_attention_decode(AttnDecArgs a, hipStream_t s);
 
 hipError_t launch_gemv_n(const GVNArgs& a, bool swiglu, hipStream_t s);

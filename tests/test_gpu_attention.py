@@ -311,6 +311,45 @@ def test_attention_decode_matches_oracle(orc, B, L, n_q, n_kv, G, ragged, hm):
     run_decode(orc, B, L, n_q, n_kv, G, ragged=ragged, qk_std=1.5, seed=B + L, hm=hm)
 
 
+@pytest.mark.parametrize("B,L,n_q,n_kv,G,hm", [
+    (64, 1024, 8, 8, 128, False),      # one head per KV head, at the split's threshold
+    (17, 2000, 64, 16, 256, True),     # two groups per KV head
+    (40, 1700, 128, 8, 2048, False),   # 16 heads per KV head
+    (2016, 260, 2, 1, 128, False),     # as many pairs as the split takes, waves that cross many of them
+])
+def test_attention_decode_balanced_split(orc, B, L, n_q, n_kv, G, hm):
+    """Large calls share the active units evenly over the waves: segments that
+    cross sequences and KV heads, empty and one-key sequences, whole KV heads
+    and sequences off, unused cache poisoned."""
+    say("attention decode balanced", B, L, n_q, n_kv, G, hm)
+    hd, ng = 128, n_q * 128 // G
+    c = synth.attn_decode_case(B + L, B, L, n_q, n_kv, hd, ng, ragged=True)
+    c.kv_len[:8] = [0, 1, 16, 17, L, L + 5, -3, L - 1]
+    c.mask[9] = 0
+    c.mask[B // 2:, ng // 2] = 0
+    k, v = c.k.copy(), c.v.copy()
+    for b in range(B):
+        n = max(0, min(int(c.kv_len[b]), L))
+        k[b, n:], v[b, n:] = 0x7FC0, 0x7FC0
+    if hm:
+        k, v = head_major(k, n_kv, hd), head_major(v, n_kv, hd)
+    q, k, v, m = (to_dev(a) for a in (c.q, k, v, c.mask))
+    ws = torch.full((W.wide_attention_decode_workspace_size(B, L, n_q, n_kv, hd, G),), 0x7F, dtype=torch.uint8,
+                    device=dev())
+    o = torch.full_like(q, float("nan"))
+    W.wide_attention_decode(q, k, v, m, n_q, n_kv, hd, G, kv_len=to_dev(c.kv_len), o=o, ws=ws, head_major=hm)
+    torch.cuda.synchronize()
+    got = to_np64(o)
+    for b in range(B) if B < 100 else np.r_[:10, B // 2:B:97, B - 1]:
+        n = max(0, min(int(c.kv_len[b]), L))
+        if n == 0:
+            assert not got[b].any() and not np.signbit(got[b]).any()
+            continue
+        args = (c.q[b:b + 1], c.k[b, :n], c.v[b, :n], c.mask[b:b + 1])
+        check_rows(got[b:b + 1], orc.attention(*args, 1, n_q, n_kv, hd, False),
+                   decode_bound(orc, *args, n_q, n_kv, hd), c.mask[b:b + 1], G, f"decode b={b} len={n}")
+
+
 @pytest.mark.parametrize("kind", ["zeros", "ones"])
 def test_attention_decode_degenerate_masks(orc, kind):
     say("attention decode mask", kind)
