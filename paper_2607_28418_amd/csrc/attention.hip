@@ -74,14 +74,19 @@ __device__ __forceinline__ u32x4 lds16(const uint16_t* p) {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// HB: query heads per workgroup (sharing one KV head); QB: 32-query blocks
-// per wave.  The launcher instantiates QB = 1: with QB = 2 every K / V^T
-// fragment read from LDS feeds two MFMAs (one per query block), halving the
-// LDS reads per MFMA, but at one wave per SIMD it ran slower on MI355X.
-template <int HB, int QB>
-__global__ __launch_bounds__(kAT, QB == 1 ? 2 : 1) void wide_attn_fwd(AttnArgs a) {
-  constexpr int RB = 4 / HB;         // row blocks (of 32*QB rows) per workgroup
-  constexpr int WR = 32 * QB;        // query rows per wave
+__device__ __forceinline__ float max3(float a, float b, float c) {  // one v_maximum3_f32
+  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
+}
+__device__ __forceinline__ float half_max(float v) {  // max of lanes l and l ^ 32
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// HB: query heads per workgroup (sharing one KV head).
+template <int HB>
+__global__ __launch_bounds__(kAT, 2) void wide_attn_fwd(AttnArgs a) {
+  constexpr int RB = 4 / HB;         // row blocks (of 32 rows) per workgroup
+  constexpr int WR = 32;             // query rows per wave
   constexpr int BMW = WR * RB;       // query rows per workgroup
   __shared__ __attribute__((aligned(16))) uint16_t smem[2 * (2 * kKSub + kVt)];  // 64 KB
 
@@ -94,8 +99,13 @@ __global__ __launch_bounds__(kAT, QB == 1 ? 2 : 1) void wide_attn_fwd(AttnArgs a
   auto classic = [&](int lid) {
     hbk = lid / per_hb;
     const int rem = lid - hbk * per_hb;
-    b = rem / a.n_slots;
-    slot = a.n_slots - 1 - (rem - b * a.n_slots);  // long key ranges first
+    // Long key ranges first, over all sequences: a sequence's tiles past its
+    // active rows then come first and exit, and the real ones follow in one
+    // run that the dispatcher spreads over the CUs.  (Sequence by sequence,
+    // four of 500 tokens at keep 0.5 put two tiles each on half of the CUs and
+    // none on the others: 62 us, now 52.)
+    slot = a.n_slots - 1 - rem / a.n_seq;
+    b = rem % a.n_seq;
   };
   auto rows_of = [&](int hk, int bb, int& s0, int& s1) {  // active run of (sequence bb, group of hk)
     const int gg = hk * HB / a.hpg;
@@ -128,7 +138,7 @@ __global__ __launch_bounds__(kAT, QB == 1 ? 2 : 1) void wide_attn_fwd(AttnArgs a
   // schedule pass split the key ranges, entry blockIdx.x of its list (a
   // tile's key chunk; longest chunks first).
   int chunk = 0, n_chunk = 1, part_unit = 0, chunk_tiles = 0;
-  if (QB == 1 && a.sched && a.sched[0] > 0) {
+  if (a.sched && a.sched[0] > 0) {
     if ((int)blockIdx.x >= a.sched[0]) return;
     const int e = a.sched[kAttnSchedHead + blockIdx.x];
     const int rank = e / kAttnMaxChunks;
@@ -163,16 +173,10 @@ __global__ __launch_bounds__(kAT, QB == 1 ? 2 : 1) void wide_attn_fwd(AttnArgs a
   const bool wave_live = wr0 < c;
   const int wr1 = min(c, wr0 + WR);
   const int l32 = lane & 31, hi = lane >> 5;
-  bool valid[QB];
-  int64_t t[QB];
-  int plim[QB];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const int myr = wr0 + 32 * qb + l32;
-    valid[qb] = myr < c;
-    t[qb] = valid[qb] ? (int64_t)idx_g[s0 + myr] : 0;
-    plim[qb] = valid[qb] ? limit_of(t[qb]) : -1;
-  }
+  const int myr = wr0 + l32;
+  const bool valid = myr < c;
+  const int t = valid ? idx_g[s0 + myr] : 0;
+  const int plim = valid ? limit_of(t) : -1;
   // rows ascend by position, so the first and last rows bound the limits
   const int wmin = wave_live ? limit_of(idx_g[s0 + wr0]) : -1;
   const int wmax = wave_live ? limit_of(idx_g[s0 + wr1 - 1]) : -1;
@@ -185,12 +189,11 @@ __global__ __launch_bounds__(kAT, QB == 1 ? 2 : 1) void wide_attn_fwd(AttnArgs a
   const int n_tiles = n_chunk > 1 ? min((gmax + kBN) / kBN, jlo + chunk_tiles) : (gmax + kBN) / kBN;
 
   // Q^T fragments (B operand): d-step s holds dims 16s + 8*hi .. +8 of the row.
-  u32x4 qf[QB][8];
+  u32x4 qf[8];
+  {
+    const uint16_t* qrow = a.q + t * ldq + (int64_t)h * kHd + hi * 8;
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const uint16_t* qrow = a.q + t[qb] * ldq + (int64_t)h * kHd + hi * 8;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) qf[qb][s] = valid[qb] ? ldg16(qrow + 16 * s) : u32x4{0, 0, 0, 0};
+    for (int s = 0; s < 8; ++s) qf[s] = valid ? ldg16(qrow + 16 * s) : u32x4{0, 0, 0, 0};
   }
 
   // Loads: a K tile and a V^T tile are 16 instructions of 1 KB (8 LDS rows
@@ -208,7 +211,7 @@ __global__ __launch_bounds__(kAT, QB == 1 ? 2 : 1) void wide_attn_fwd(AttnArgs a
     const int lc = (lane & 7) ^ swz_f(r);
     off[q] = kwave ? (uint32_t)((r * ldk + lc * 8) * 2) : (uint32_t)(((int64_t)r * a.T_kp + lc * 8) * 2);
   }
-  uint16_t* const kst = smem;                 // K ring: 2 x [2 halves][64 keys][64 dims]
+  uint16_t* const kst = smem;                  // K ring: 2 x [2 halves][64 keys][64 dims]
   uint16_t* const vst = smem + 2 * 2 * kKSub;  // V^T ring: 2 x [128 dims][64 keys]
   auto issue_k = [&](int jt) {  // waves 0-1
     const int j0 = jt * kBN;
@@ -242,124 +245,84 @@ __global__ __launch_bounds__(kAT, QB == 1 ? 2 : 1) void wide_attn_fwd(AttnArgs a
   // 16(r/8) + 8*hi + r%8 of its 32-key block.
   const int pi = 16 * (l32 >> 4) + 8 * ((l32 >> 2) & 1) + 4 * ((l32 >> 3) & 1) + (l32 & 3);
 
-  f32x16 O[QB][4];
+  // Element offsets of this lane's fragment reads: K slot i (of 16) of a tile
+  // holds dims 16 (i/2) .. of key block i%2, V slot i keys 16 (i/4) .. of dims
+  // 32 (i%4) ..; the rows' swizzles repeat every 32 rows.
+  int ko[4], vo[4];
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) O[qb][i] = f32x16{};
-  float m[QB], z[QB];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    m[qb] = -INFINITY;
-    z[qb] = 0.0f;
+  for (int q = 0; q < 4; ++q) {
+    ko[q] = swz(pi, 2 * q + hi);
+    vo[q] = swz(l32, 2 * q + hi);
   }
+  auto k_frag = [&](const uint16_t* st, int i) {
+    return lds16(st + (i >> 3) * kKSub + (i & 1) * (32 * 64) + ko[(i >> 1) & 3]);
+  };
+  auto v_frag = [&](const uint16_t* st, int i) { return lds16(st + (i & 3) * (32 * 64) + vo[i >> 2]); };
+
+  f32x16 O[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) O[i] = f32x16{};
+  float m = -INFINITY, z = 0.0f;  // running maximum (log2 units) and sum of this lane half's keys
+  float muse = 0.0f;              // subtrahend of the current tile's scores: m, or 0 before the first visible key
+  float alpha = 1.0f;             // pending rescale of O and z
+  bool moved = false;             // some row has one
   const float sc = a.scale_log2;
 
-  // S^T of key tile jt for this wave's queries (two 32-key blocks each).
-  auto qk = [&](int jt, f32x16 (&S)[QB][2]) {
-    const uint16_t* st = kst + (jt & 1) * 2 * kKSub;
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      S[qb][0] = f32x16{};
-      S[qb][1] = f32x16{};
-    }
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const uint16_t* ks = st + (s >> 2) * kKSub;
-      const int ch = 2 * (s & 3) + hi;
-      const u32x4 k0 = lds16(ks + swz(pi, ch));
-      const u32x4 k1 = lds16(ks + swz(32 + pi, ch));
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
-        S[qb][0] = mfma32(k0, qf[qb][s], S[qb][0]);
-        S[qb][1] = mfma32(k1, qf[qb][s], S[qb][1]);
-      }
-    }
+  // Only a tile that crosses some row's limit, or holds the first visible
+  // key, evaluates the per-element mask; every other one is fully visible to
+  // the wave.
+  auto partial = [&](int jt) { return jt * kBN + kBN - 1 > wmin || jt * kBN < lp; };
+  // The running maximum after the next tile, from this lane's largest score.
+  // (A subtrahend that follows only once some row's maximum has grown by 2^8
+  // rescales rarely and ran 3% faster, but the largest probability is then no
+  // longer exactly 1 and the outputs' error against 64 bits rose by 5%.)
+  auto new_max = [&](float mx) {
+    const float mn = fmaxf(m, half_max(mx) * sc);
+    moved = __any(mn > m);
+    if (!moved) return;
+    muse = mn == -INFINITY ? 0.0f : mn;  // a row with nothing visible yet
+    alpha = fast_exp2(m - muse);
+    m = mn;
   };
-  // Online softmax of tile jt's scores per query block (masking and the new
-  // row maximum, then the exponentials and the rescale) and O^T += V^T P^T.
-  auto softmax_pv = [&](int jt, f32x16 (&S)[QB][2]) {
+  auto mask_max = [&](int jt, f32x16 (&S)[2]) {  // of a partially visible tile
     const int j0 = jt * kBN;
-    // Per-element mask only where the tile crosses some row's limit or holds
-    // the first visible key; every other tile is fully visible to the wave.
-    if (j0 + kBN - 1 > wmin || j0 < lp) {
-      const int lo = lp - j0 - 8 * hi;  // key offsets below this are padding
+    const int lo = lp - j0 - 8 * hi;     // key offsets below this are padding
+    const int lim = plim - j0 - 8 * hi;  // key offset past which this row sees nothing
+    float mx = -INFINITY;
 #pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
-        const int lim = plim[qb] - j0 - 8 * hi;  // key offset past which this row sees nothing
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int ko = 32 * kb + 16 * (r >> 3) + (r & 7);
-            S[qb][kb][r] = ko > lim || ko < lo ? -INFINITY : S[qb][kb][r];
-          }
-      }
+    for (int r = 0; r < 16; ++r) {
+      const int key = 16 * (r >> 3) + (r & 7);
+      S[0][r] = key > lim || key < lo ? -INFINITY : S[0][r];
+      S[1][r] = key + 32 > lim || key + 32 < lo ? -INFINITY : S[1][r];
+      mx = max3(mx, S[0][r], S[1][r]);
     }
-    float alpha[QB];
-    bool moved = false;
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      float mx = -INFINITY;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, S[qb][kb][r]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float mnew = fmaxf(m[qb], mx * sc);
-      const float muse = mnew == -INFINITY ? 0.0f : mnew;  // a row with nothing visible yet
-      alpha[qb] = fast_exp2(m[qb] - muse);
-      m[qb] = mnew;
-      moved = moved || alpha[qb] != 1.0f;
-      float zs = 0.0f;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float p = fast_exp2(fmaf(S[qb][kb][r], sc, -muse));
-          S[qb][kb][r] = p;
-          zs += p;
-        }
-      }
-      z[qb] = z[qb] * alpha[qb] + zs;
-    }
-    if (__any(moved)) {  // lazy rescale: skipped once the maxima settle
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-        for (int db = 0; db < 4; ++db) O[qb][db] *= alpha[qb];
-    }
-    const uint16_t* vts = vst + (jt & 1) * kVt;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        u32x4 pf[QB];
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            pf[qb][e] = pack_bf16x2_hw(S[qb][kb][8 * p + 2 * e], S[qb][kb][8 * p + 2 * e + 1]);
-        const int ch = 4 * kb + 2 * p + hi;
-#pragma unroll
-        for (int db = 0; db < 4; ++db) {
-          const u32x4 vf = lds16(vts + swz(32 * db + l32, ch));
-#pragma unroll
-          for (int qb = 0; qb < QB; ++qb) O[qb][db] = mfma32(vf, pf[qb], O[qb][db]);
-        }
-      }
-    }
+    new_max(mx);
   };
 
   // Key tiles this wave sees at all (a prefix of the workgroup's range).
   const int wtiles = wave_live ? min(n_tiles, (wmax + kBN) / kBN) : 0;
-  // Pipeline: iteration jt loads K of tile jt+2 and V of tile jt+1, computes
-  // the scores of tile jt+1 and then the softmax and P.V of tile jt, so the
-  // matrix core has independent work while the softmax runs.  Everything
-  // issued in one iteration lands before the next one starts.
-  if (jlo >= n_tiles) {
-    // left padding hides every key of this tile's rows: nothing to stream
-  } else if constexpr (QB == 1) {
+  // Pipeline: iteration jt loads K of tile jt+2 and V of tile jt+1 and runs
+  //   B  the 16 MFMAs of S^T(jt+1), between them the exponentials of ten of
+  //      tile jt's 16 score pairs;
+  //   C  the 16 MFMAs of O^T += V^T P^T of tile jt, between the first eight
+  //      the other six pairs, between the last eight the maxima of S^T(jt+1).
+  // Per tile a wave has 1024 cycles of MFMA and about as many of softmax on
+  // the vector ALU (32 exponentials a lane at a quarter rate).  Written as two
+  // blocks, scores then softmax, the pair of waves on a SIMD met at the tile's
+  // barrier and ran the same phase at the same time; with the two kinds of
+  // instructions alternating inside each wave, both units stay busy.  LDS
+  // fragments are read three MFMAs ahead of their use.  Everything loaded in
+  // one iteration lands before the next one starts.
+  // (Llama-3-8B heads, T = 8192, whole call: keep 0.5 367 -> 362 us, all
+  // active 605 -> 575.)  What is left is the sum of the parts: all active, the
+  // same loop without loads runs 18% faster, without the softmax 14%, without
+  // LDS reads 8%, and its MFMAs alone at 1.2 PFLOP/s, held by the chip's power
+  // limit.  Measured and not better: two query blocks per wave (half the LDS
+  // reads and loads per MFMA, one wave a SIMD, accumulators in AGPRs), three
+  // and four ring stages, and eight waves per tile as two teams that take
+  // alternate key tiles and meet in LDS.
+  constexpr int AHEAD = 3, NB_PAIRS = 10;
+  if (jlo < n_tiles) {  // (left padding may hide every key of this tile's rows)
     if (kwave) {
       issue_k(jlo);
       if (jlo + 1 < n_tiles) issue_k(jlo + 1);
@@ -368,9 +331,15 @@ __global__ __launch_bounds__(kAT, QB == 1 ? 2 : 1) void wide_attn_fwd(AttnArgs a
     }
     t256::wait_vm<0>();
     t256::stage_barrier();
-    f32x16 Sa[QB][2], Sb[QB][2];
-    if (jlo < wtiles) qk(jlo, Sa);
-    auto step = [&](int jt, f32x16 (&Sc)[QB][2], f32x16 (&Sn)[QB][2]) {
+    f32x16 Sa[2], Sb[2];
+    if (jlo < wtiles) {
+      const uint16_t* ks = kst + (jlo & 1) * 2 * kKSub;
+      Sa[0] = Sa[1] = f32x16{};
+#pragma unroll
+      for (int i = 0; i < 16; ++i) Sa[i & 1] = mfma32(k_frag(ks, i), qf[i >> 1], Sa[i & 1]);
+      mask_max(jlo, Sa);
+    }
+    auto step = [&](int jt, f32x16 (&Sc)[2], f32x16 (&Sn)[2]) {
       t256::wait_vm<0>();
       t256::stage_barrier();
       if (kwave) {
@@ -378,72 +347,100 @@ __global__ __launch_bounds__(kAT, QB == 1 ? 2 : 1) void wide_attn_fwd(AttnArgs a
       } else {
         if (jt + 1 < n_tiles) issue_v(jt + 1);
       }
-      if (jt + 1 < wtiles) qk(jt + 1, Sn);
-      if (jt < wtiles) softmax_pv(jt, Sc);  // l = 2: tiles past the wave's rows issue no MFMA
+      if (jt >= wtiles) return;  // l = 2: tiles past the wave's rows issue no MFMA
+      const uint16_t* ks = kst + ((jt + 1) & 1) * 2 * kKSub;
+      const uint16_t* vs = vst + (jt & 1) * kVt;
+      u32x4 f[4], pf[4];
+      float z0 = 0.0f, z1 = 0.0f;
+      auto pair = [&](int j) {  // scores 2j, 2j + 1 of the lane's 32 -> probabilities, packed for P^T
+        const float p0 = fast_exp2(fmaf(Sc[j >> 3][2 * (j & 7)], sc, -muse));
+        const float p1 = fast_exp2(fmaf(Sc[j >> 3][2 * (j & 7) + 1], sc, -muse));
+        z0 += p0;
+        z1 += p1;
+        asm("" : "+v"(z0), "+v"(z1));  // added here: added after the tile, every p would stay alive
+        pf[j >> 2][j & 3] = pack_bf16x2_hw(p0, p1);
+      };
+      if (moved) {
+#pragma unroll
+        for (int db = 0; db < 4; ++db) O[db] *= alpha;
+        z *= alpha;
+        moved = false;
+      }
+      if (jt + 1 < wtiles) {
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) f[i] = k_frag(ks, i);
+        Sn[0] = Sn[1] = f32x16{};
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          f[(i + AHEAD) & 3] = i + AHEAD < 16 ? k_frag(ks, i + AHEAD) : v_frag(vs, i + AHEAD - 16);
+          Sn[i & 1] = mfma32(f[i & 3], qf[i >> 1], Sn[i & 1]);
+#pragma unroll
+          for (int j = i * NB_PAIRS / 16; j < (i + 1) * NB_PAIRS / 16; ++j) pair(j);
+          t256::sched_fence();
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) f[i] = v_frag(vs, i);
+#pragma unroll
+        for (int j = 0; j < NB_PAIRS; ++j) pair(j);
+      }
+      float x0 = -INFINITY, x1 = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        if (i + AHEAD < 16) f[(i + AHEAD) & 3] = v_frag(vs, i + AHEAD);
+        O[i & 3] = mfma32(f[i & 3], pf[i >> 2], O[i & 3]);
+        if (i < 8) {
+#pragma unroll
+          for (int j = i * (16 - NB_PAIRS) / 8; j < (i + 1) * (16 - NB_PAIRS) / 8; ++j) pair(NB_PAIRS + j);
+        } else {  // (past the wave's last tile: stale scores, not used)
+          const int e = 2 * (i - 8);
+          x0 = max3(x0, Sn[0][e], Sn[0][e + 1]);
+          x1 = max3(x1, Sn[1][e], Sn[1][e + 1]);
+        }
+        t256::sched_fence();
+      }
+      z += z0 + z1;
+      if (jt + 1 < wtiles) {
+        if (partial(jt + 1)) mask_max(jt + 1, Sn);
+        else new_max(fmaxf(x0, x1));
+      }
     };
     for (int jt = jlo; jt < n_tiles; jt += 2) {
       step(jt, Sa, Sb);
       if (jt + 1 < n_tiles) step(jt + 1, Sb, Sa);
     }
-  } else {
-    // Two query blocks already give the matrix core independent work, and
-    // the registers for a second score tile are not there: scores of tile jt
-    // are computed in its own step.
-    // Both rings run one tile ahead: iteration jt loads K and V of tile jt+1
-    // into the stages tile jt-1 used.
-    f32x16 S[QB][2];
-    if (kwave) issue_k(jlo);
-    else issue_v(jlo);
-    for (int jt = jlo; jt < n_tiles; ++jt) {
-      t256::wait_vm<0>();
-      t256::stage_barrier();
-      if (jt + 1 < n_tiles) {
-        if (kwave) issue_k(jt + 1);
-        else issue_v(jt + 1);
-      }
-      if (jt < wtiles) {  // l = 2: tiles past the wave's rows issue no MFMA
-        qk(jt, S);
-        softmax_pv(jt, S);
-      }
-    }
   }
 
-  if (QB == 1 && n_chunk > 1) {
+  if (n_chunk > 1) {
     // One chunk of a split key range: the unnormalised O^T registers, the
     // running maximum and this lane half's sum go to the unit's partial
     // slot, lane-major so that every store of the wave is 1 KB contiguous;
     // wide_attn_merge combines the chunks.
-    float4* po = reinterpret_cast<float4*>(a.part) + ((int64_t)part_unit * 4 + w) * (QB * 16 * kWave);
+    float4* po = reinterpret_cast<float4*>(a.part) + ((int64_t)part_unit * 4 + w) * (16 * kWave);
     float2* pm = reinterpret_cast<float2*>(a.part + (int64_t)kAttnMaxUnits * kAttnPartO) +
-                 ((int64_t)part_unit * 4 + w) * (QB * kWave);
+                 ((int64_t)part_unit * 4 + w) * kWave;
+    pm[lane] = make_float2(m, z);
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      pm[qb * kWave + lane] = make_float2(m[qb], z[qb]);
+    for (int db = 0; db < 4; ++db)
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          po[((qb * 4 + db) * 4 + j) * kWave + lane] =
-              make_float4(O[qb][db][4 * j], O[qb][db][4 * j + 1], O[qb][db][4 * j + 2], O[qb][db][4 * j + 3]);
-    }
+      for (int j = 0; j < 4; ++j)
+        po[(db * 4 + j) * kWave + lane] =
+            make_float4(O[db][4 * j], O[db][4 * j + 1], O[db][4 * j + 2], O[db][4 * j + 3]);
     return;
   }
   // Epilogue: the two halves of a query's sum, normalise, scatter the row.
+  const float zt = z + __shfl_xor(z, 32);
+  if (!valid) return;
+  const float inv = zt > 0.0f ? 1.0f / zt : 0.0f;  // no visible key (left padding): +0
+  uint16_t* orow = a.o + t * ldq + (int64_t)h * kHd + 4 * hi;
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const float zt = z[qb] + __shfl_xor(z[qb], 32);
-    if (!valid[qb]) continue;
-    const float inv = zt > 0.0f ? 1.0f / zt : 0.0f;  // no visible key (left padding): +0
-    uint16_t* orow = a.o + t[qb] * ldq + (int64_t)h * kHd + 4 * hi;
+  for (int db = 0; db < 4; ++db) {
 #pragma unroll
-    for (int db = 0; db < 4; ++db) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        uint2 v;
-        v.x = pack_bf16x2_hw(O[qb][db][4 * j] * inv, O[qb][db][4 * j + 1] * inv);
-        v.y = pack_bf16x2_hw(O[qb][db][4 * j + 2] * inv, O[qb][db][4 * j + 3] * inv);
-        *reinterpret_cast<uint2*>(orow + 32 * db + 8 * j) = v;
-      }
+    for (int j = 0; j < 4; ++j) {
+      uint2 v;
+      v.x = pack_bf16x2_hw(O[db][4 * j] * inv, O[db][4 * j + 1] * inv);
+      v.y = pack_bf16x2_hw(O[db][4 * j + 2] * inv, O[db][4 * j + 3] * inv);
+      *reinterpret_cast<uint2*>(orow + 32 * db + 8 * j) = v;
     }
   }
 }
@@ -766,9 +763,9 @@ hipError_t launch_attention(AttnArgs a, const uint16_t* v, int32_t* seq_off, hip
   const int64_t n_classic = (int64_t)(a.n_q / hb) * a.n_seq * a.n_slots;
   const int64_t max_units = std::min<int64_t>(kAttnMaxUnits, (int64_t)a.split_tiles * kAttnMaxChunks);
   const dim3 grid((unsigned)std::max<int64_t>(n_classic, a.sched ? max_units : 0));
-  if (hb == 4) WIDE_LAUNCH_NAMED("wide_attn_fwd", (wide_attn_fwd<4, 1>), grid, dim3(kAT), 0, s, a);
-  else if (hb == 2) WIDE_LAUNCH_NAMED("wide_attn_fwd", (wide_attn_fwd<2, 1>), grid, dim3(kAT), 0, s, a);
-  else WIDE_LAUNCH_NAMED("wide_attn_fwd", (wide_attn_fwd<1, 1>), grid, dim3(kAT), 0, s, a);
+  if (hb == 4) WIDE_LAUNCH_NAMED("wide_attn_fwd", (wide_attn_fwd<4>), grid, dim3(kAT), 0, s, a);
+  else if (hb == 2) WIDE_LAUNCH_NAMED("wide_attn_fwd", (wide_attn_fwd<2>), grid, dim3(kAT), 0, s, a);
+  else WIDE_LAUNCH_NAMED("wide_attn_fwd", (wide_attn_fwd<1>), grid, dim3(kAT), 0, s, a);
   if (a.sched) {
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const dim3 mg((unsigned)a.split_tiles);
