@@ -13,6 +13,8 @@
 // differs (tile256.h).  Tiles whose 256 rows are all active take the
 // all-active path (no per-fragment tests), as the paper does for full tiles
 // of a sorted column.  BK is the ring's k depth, 64.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 #include "launch.h"
@@ -29,6 +31,10 @@ __device__ __attribute__((aligned(16))) uint16_t g_zero_blk[64];  // stays zero:
 // dense-masked K-axis kernel over more than 128 groups, which keeps 17 KB for
 // its tile's mask bits and so runs two A stages.
 using RingMN = Ring<3>;
+// 128-wide N-axis tiles (NFN = 2): B stages are half as large, and four of
+// them fit.
+template <int NFN>
+using RingN = std::conditional_t<NFN == 2, Ring<3, 4, 2>, RingMN>;
 template <int NWR>
 using RingKD = Ring<NWR == 0 ? 2 : 3>;
 
@@ -79,8 +85,8 @@ __host__ __device__ __forceinline__ int mn256_share(int tiles) { return (tiles +
 // `act` tile rows are active, always a prefix (rows past the active count, or
 // past M, come last in a tile).
 template <class Rg, int BL, class Koff, class LdA, class LdB>
-__device__ __forceinline__ void run_tile(uint16_t* smem, int nsteps, Koff koff, LdA lda, LdB ldb, const int (&bb)[4],
-                                         int64_t act, f32x16 (&acc)[4][4]) {
+__device__ __forceinline__ void run_tile(uint16_t* smem, int nsteps, Koff koff, LdA lda, LdB ldb,
+                                         const int (&bb)[Rg::NFN], int64_t act, f32x16 (&acc)[4][Rg::NFN]) {
   const int p = (int)(act < 0 ? 0 : act > BM ? BM : act);
   const int w = wave_id(), wm = w >> 1;
   const int nl = min(4, max(0, (p - wm * 128 + 31) / 32));  // live A fragments of the wave
@@ -122,24 +128,33 @@ __device__ __forceinline__ bool mn256_ordered(const MN256Args& a, const MN256Reg
          share % per_group == 0;
 }
 
-// "m-blocked" (gate/up): when an XCD's share is a whole number of groups, it
-// runs m-tile 0 of each of its groups, then m-tile 1, and so on, over one
-// half of its groups and then the other.  The tiles that run together then
-// gather rows from one stretch of tokens (a sorted m-tile of any group
-// covers about the same token range) instead of one group's whole token
-// list, so the gathered rows are mostly shared in L2 while each group's
-// weight panel is re-read once per m-tile.  Measured on the Llama-3-8B
-// gate/up at T = 8192 (topk, keep 0.5): traffic from beyond L2 down 37%,
-// time down 2% against group by group; blocks of 4 or 8 m-tiles per group
-// cut the traffic as much but ran 7-9% slower.  Halves (7 of the XCD's 14
-// groups at a time, so fewer weight panels per k step, and the first
-// half's partial m-tiles run beside the second half's full ones) took
-// another 2.5% off; pairs of groups did the same.
+// "m-blocked" (gate/up): each XCD takes an eighth of the column tiles and runs
+// m-tile 0 of each of them, then m-tile 1, and so on, over one half of its
+// columns and then the other.  The tiles that run together then gather rows
+// from one stretch of tokens (a sorted m-tile of any group covers about the
+// same token range) instead of one group's whole token list, so the gathered
+// rows are mostly shared in L2 while each group's weight panel is re-read once
+// per m-tile.  Measured on the Llama-3-8B gate/up at T = 8192 (topk, keep
+// 0.5): traffic from beyond L2 down 37%, time down 2% against group by group;
+// blocks of 4 or 8 m-tiles per group cut the traffic as much but ran 7-9%
+// slower.  Halves (7 of the XCD's 14 groups at a time, so fewer weight panels
+// per k step, and the first half's partial m-tiles run beside the second
+// half's full ones) took another 2.5% off; pairs of groups did the same.  It
+// also deals the real tiles in one run: workgroups go round-robin to an
+// XCD's four shader engines, and real and empty tiles in turn (two m-tiles
+// per group, one empty) sent all the real ones to two of them (Llama-7B
+// gate/up, 300 tokens, 64-column tiles: 106 us, now 65).  Launches on
+// 64-column tiles, at most one round, take no halves.
 template <int BNO>
-__device__ __forceinline__ bool mn256_mblocked(const MN256Args& a, const MN256Region& R) {
-  const int share = mn256_share(R.tiles), per_group = R.gw / BNO * a.m_tiles;
-  return a.mblock && R.masked == kMN256Sorted && R.gw / BNO <= 4 && 8 * share == R.tiles &&
-         share % per_group == 0;
+__host__ __device__ __forceinline__ bool mn256_mblocked(const MN256Args& a, const MN256Region& R) {
+  return a.mblock && R.masked == kMN256Sorted && (BNO == 64 || R.gw <= (BNO <= 128 ? 512 : 1024));
+}
+
+// Workgroups per XCD of a region.
+template <int BNO>
+__host__ __device__ __forceinline__ int mn256_region_share(const MN256Args& a, const MN256Region& R) {
+  if (mn256_mblocked<BNO>(a, R)) return (R.tiles / a.m_tiles + 7) / 8 * a.m_tiles;
+  return mn256_share(R.tiles);
 }
 
 template <int BNO>
@@ -150,13 +165,24 @@ __device__ __forceinline__ void mn256_coords(const MN256Args& a, const MN256Regi
   const int ntpg = R.gw / BNO;  // tiles per group
   const int per_group = ntpg * a.m_tiles;
   if (mn256_mblocked<BNO>(a, R)) {
-    // the XCD's groups in two halves, each walked m-tile by m-tile
-    const int gps = share / per_group, parts = gps % 2 == 0 && gps >= 4 ? 2 : 1, gpp = gps / parts;
-    const int per_part = gpp * ntpg * a.m_tiles, part = local / per_part, l = local % per_part;
-    const int r = l % (gpp * ntpg);
-    m_tile = l / (gpp * ntpg);
-    g = xcd * gps + part * gpp + r / ntpg;
-    nt_in = r % ntpg;
+    // the XCD's column tiles [c0, c0 + n) in two halves, each walked m-tile by
+    // m-tile (m_tile = a.m_tiles: padding)
+    const int cols = R.tiles / a.m_tiles;
+    int c0 = cols * xcd / 8, n = cols * (xcd + 1) / 8 - c0, l = local;
+    if (BNO != 64 && n >= 4 * ntpg) {
+      const int h = n / 2;
+      if (l < h * a.m_tiles) {
+        n = h;
+      } else {
+        l -= h * a.m_tiles;
+        c0 += h;
+        n -= h;
+      }
+    }
+    m_tile = n ? min(l / n, a.m_tiles) : a.m_tiles;
+    const int col = c0 + (n ? l % n : 0);
+    g = col / ntpg;
+    nt_in = col % ntpg;
     return;
   }
   if (mn256_ordered<BNO>(a, R)) {
@@ -206,10 +232,11 @@ __device__ __forceinline__ void mn256_coords(const MN256Args& a, const MN256Regi
   }
 }
 
-__device__ __forceinline__ int mn256_shares(const MN256Args& a) {
-  int n = mn256_share(a.reg[0].tiles);
-  if (a.n_regions > 1) n += mn256_share(a.reg[1].tiles);
-  if (a.n_regions > 2) n += mn256_share(a.reg[2].tiles);
+template <int BNO>
+__host__ __device__ __forceinline__ int mn256_shares(const MN256Args& a) {
+  int n = mn256_region_share<BNO>(a, a.reg[0]);
+  if (a.n_regions > 1) n += mn256_region_share<BNO>(a, a.reg[1]);
+  if (a.n_regions > 2) n += mn256_region_share<BNO>(a, a.reg[2]);
   return n;
 }
 
@@ -275,13 +302,15 @@ __device__ __forceinline__ void mn256_chunk_steps(int K, int c, int n, int& s0, 
 }
 
 // --------------------------------------------------------------------- GEMM-MN
-template <bool SWIGLU, int BK, bool BUF>
-__global__ __launch_bounds__(NT, 1) void wide_mn256(MN256Args a) {
-  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+// NFN = 2 (gate/up only): tiles of 128 weight rows, 64 output columns (see
+// wide_mn256_fit).
+template <bool SWIGLU, int BK, bool BUF, int NFN>
+__device__ __forceinline__ void mn256_run(const MN256Args& a, uint16_t* smem) {
   static_assert(BK == t256::BK, "64-deep ring");
-  using Rg = RingMN;
-  constexpr int S = Rg::SLOTS;
-  constexpr int BNO = SWIGLU ? 128 : 256;  // output columns per tile
+  using Rg = RingN<NFN>;
+  constexpr int S = Rg::SLOTS, SB = Rg::BSLOTS;
+  constexpr int BNO = (SWIGLU ? 32 : 64) * NFN;  // output columns per tile
+  constexpr int WROWS = BNO;                     // rows of one weight panel
   const uint16_t* zero = g_zero_blk;
 
   // Workgroups are dealt round-robin to the 8 XCDs.  Each region's tiles
@@ -292,10 +321,10 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256(MN256Args a) {
   // holding K and V with half again the work of the others).
   const int xcd = blockIdx.x % 8;
   int local = blockIdx.x / 8;
-  const int shares = mn256_shares(a);
   int ri = 0, job = -1;   // region; tail job of a tail block
   int chunk = 0, nchunks = 1;
-  if (local >= shares) {  // one of the 32 tail blocks per XCD
+  if (NFN == 2) {  // one region, no tail
+  } else if (const int shares = mn256_shares<BNO>(a); local >= shares) {  // one of the 32 tail blocks per XCD
     job = local - shares;
     const MN256Tail t = mn256_tail<BNO>(a, xcd);
     if (job >= t.n * t.split) return;
@@ -304,11 +333,11 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256(MN256Args a) {
     mn256_tail_tile(t, job / t.split, ri, local);
   } else {
     ri = 0;
-    if (a.n_regions > 1 && local >= mn256_share(a.reg[0].tiles)) {
-      local -= mn256_share(a.reg[0].tiles);
+    if (a.n_regions > 1 && local >= mn256_region_share<BNO>(a, a.reg[0])) {
+      local -= mn256_region_share<BNO>(a, a.reg[0]);
       ri = 1;
-      if (a.n_regions > 2 && local >= mn256_share(a.reg[1].tiles)) {
-        local -= mn256_share(a.reg[1].tiles);
+      if (a.n_regions > 2 && local >= mn256_region_share<BNO>(a, a.reg[1])) {
+        local -= mn256_region_share<BNO>(a, a.reg[1]);
         ri = 2;
       }
     }
@@ -319,12 +348,12 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256(MN256Args a) {
       if (local < real && before + local >= t.base) return;
     }
   }
-  const MN256Region R = ri == 0 ? a.reg[0] : ri == 1 ? a.reg[1] : a.reg[2];
-  const int share = mn256_share(R.tiles);
-  const int tile = xcd * share + local;
-  if (tile >= R.tiles) return;  // padding
+  MN256Region R = ri == 0 ? a.reg[0] : ri == 1 ? a.reg[1] : a.reg[2];
+  if (NFN == 2) R.tiles *= 2;
+  if (!mn256_mblocked<BNO>(a, R) && xcd * mn256_share(R.tiles) + local >= R.tiles) return;  // padding
   int g, nt_in, m_tile;
   mn256_coords<BNO>(a, R, xcd, local, g, m_tile, nt_in);
+  if (m_tile >= a.m_tiles) return;  // padding
   const int n0 = g * R.gw + nt_in * BNO;
   const int64_t M = a.M;
   const int K = a.K;
@@ -375,35 +404,36 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256(MN256Args a) {
   // read zeros.  Under SwiGLU waves 0 and 1 load gate rows, 2 and 3 up rows.
   const uint16_t* wpanel = uniform_ptr((SWIGLU && wave_id() >= 2 ? R.w1 : R.w0) + (int64_t)n0 * K);
   const bufview_t va = buf_view(uniform_ptr(a.x), BUF ? (uint32_t)(M * K * 2) : 0u);
-  const bufview_t vb = buf_view(wpanel, BUF ? (uint32_t)((SWIGLU ? 128 : 256) * K * 2) : 0u);
-  uint32_t aoff[S], boff[S];
+  const bufview_t vb = buf_view(wpanel, BUF ? (uint32_t)(WROWS * K * 2) : 0u);
+  uint32_t aoff[S], boff[SB];
   const uint16_t* abase[S];
-  const uint16_t* bbase[S];
+  const uint16_t* bbase[SB];
 #pragma unroll
   for (int j = 0; j < S; ++j) {
     const int rr = Rg::slot_row(j);
     const int c8 = Rg::slot_chunk(j) * 8;
     const int64_t p = m0 + rr;
     const int64_t arow = p < cnt ? (rows ? (int64_t)rows[p] : p) : -1;
-    const int64_t brow = SWIGLU ? (rr & 127) : rr;
-    if (BUF) {
-      aoff[j] = arow >= 0 ? (uint32_t)((arow * K + c8) * 2) : kOffDead;
-      boff[j] = (uint32_t)((brow * K + c8) * 2);
-    } else {
-      abase[j] = arow >= 0 ? a.x + arow * K + c8 : nullptr;
-      bbase[j] = wpanel + brow * K + c8;
-    }
+    if (BUF) aoff[j] = arow >= 0 ? (uint32_t)((arow * K + c8) * 2) : kOffDead;
+    else abase[j] = arow >= 0 ? a.x + arow * K + c8 : nullptr;
   }
-  // B fragments of the wave: SwiGLU pairs gate column c (B rows 0..127) with
-  // up column c (B rows 128..255), so a wave takes 64 gate rows (fragments 0
-  // and 1) and the same 64 up rows (fragments 2 and 3)
+#pragma unroll
+  for (int j = 0; j < SB; ++j) {
+    const int64_t brow = Rg::slot_row(j, SB) & (WROWS - 1);
+    const int c8 = Rg::slot_chunk(j, SB) * 8;
+    if (BUF) boff[j] = (uint32_t)((brow * K + c8) * 2);
+    else bbase[j] = wpanel + brow * K + c8;
+  }
+  // B fragments of the wave: SwiGLU pairs gate column c (the tile's first half
+  // of B rows) with up column c (the second half), so a wave takes 16 NFN gate
+  // rows (the first NFN / 2 fragments) and the same up rows (the others)
   const int wn = wave_id() & 1;
   constexpr int BL = SWIGLU ? 1 : 0;
-  int bb[4];
+  int bb[NFN];
 #pragma unroll
-  for (int fn = 0; fn < 4; ++fn) bb[fn] = (SWIGLU ? wn * 64 : wn * 128) + bfrag_off<BL>(fn);
+  for (int fn = 0; fn < NFN; ++fn) bb[fn] = wn * (SWIGLU ? 16 : 32) * NFN + bfrag_off<BL, NFN>(fn);
 
-  f32x16 acc[4][4];
+  f32x16 acc[4][NFN];
   zero_acc(acc);
   int s0 = 0, ns = K / BK;  // a tail chunk runs its share of the k steps
   if (job >= 0) mn256_chunk_steps<BK>(K, chunk, nchunks, s0, ns);
@@ -413,8 +443,8 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256(MN256Args a) {
     else Rg::issue_ptr(st, abase[j] ? abase[j] + k0 : zero, j);
   };
   auto ldb = [&](uint16_t* st, int k0, int j) {
-    if (BUF) Rg::issue_buf(st, vb, boff[j], 2u * k0, j);
-    else Rg::issue_ptr(st, bbase[j] + k0, j);
+    if (BUF) Rg::issue_buf(st, vb, boff[j], 2u * k0, j, SB);
+    else Rg::issue_ptr(st, bbase[j] + k0, j, SB);
   };
   int my_row = -1;
   if (job < 0 && tid < BM && m0 + tid < M) my_row = rows ? rows[m0 + tid] : (int)(m0 + tid);
@@ -422,7 +452,7 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256(MN256Args a) {
   run_tile<Rg, BL>(smem, ns, koff, lda, ldb, bb, cnt - m0, acc);
   const int col = acc_col();
 
-  if (job >= 0) {  // tail chunk: fp32 partial tile [256 rows][256 B-tile rows]
+  if (NFN == 4 && job >= 0) {  // tail chunk: fp32 partial tile [256 rows][256 B-tile rows]
     float* P = a.tail_ws + ((int64_t)xcd * kMN256TailJobs + job) * (BM * BN);
 #pragma unroll
     for (int fm = 0; fm < 4; ++fm)
@@ -430,7 +460,7 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256(MN256Args a) {
       for (int i = 0; i < 16; ++i) {
         const int r = acc_row(fm, i);
 #pragma unroll
-        for (int fn = 0; fn < 4; ++fn) P[r * BN + bb[fn] + col] = acc[fm][fn][i];
+        for (int fn = 0; fn < NFN; ++fn) P[r * BN + bb[fn] + col] = acc[fm][fn][i];
       }
     return;
   }
@@ -444,7 +474,7 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256(MN256Args a) {
   // gate/up 3%; staged, gate/up is 1.5% faster).
   const int* map = stage_row_map(smem, my_row, (int)rbits);
   const int gsh = tok_order ? __builtin_ctz(a.mask_G) : 0;
-  constexpr int NO = SWIGLU ? 2 : 4;  // output fragments of the wave
+  constexpr int NO = SWIGLU ? NFN / 2 : NFN;  // output fragments of the wave
   constexpr int PITCH = BNO + 8;      // bf16 per staged row
   static_assert(2 * BM * (int)sizeof(int) + BM * PITCH * 2 <= Rg::LDS, "row map and staged tile fit the ring");
   uint16_t* ot = smem + 2 * BM * (int)(sizeof(int) / sizeof(uint16_t));
@@ -458,7 +488,7 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256(MN256Args a) {
       for (int fn = 0; fn < NO; ++fn) {
         const int c = bb[fn] + col;  // output column in the tile
         const bool on = !tok_order || ((rb >> (c >> gsh)) & 1);
-        const float v = SWIGLU ? silu(acc[fm][fn][i]) * acc[fm][fn + 2][i] : acc[fm][fn][i];
+        const float v = SWIGLU ? silu(acc[fm][fn][i]) * acc[fm][fn + NFN / 2][i] : acc[fm][fn][i];
         ot[r * PITCH + c] = f32_to_bf16_hw(on ? v : 0.f);
       }
     }
@@ -471,6 +501,45 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256(MN256Args a) {
     const int t = map[r];
     if (t >= 0)
       stg16(R.out + (int64_t)t * R.ldo + n0 + c8 * 8, *reinterpret_cast<const u32x4*>(ot + r * PITCH + c8 * 8));
+  }
+}
+
+template <bool SWIGLU, int BK, bool BUF>
+__global__ __launch_bounds__(NT, 1) void wide_mn256(MN256Args a) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  mn256_run<SWIGLU, BK, BUF, 4>(a, smem);
+}
+
+// Gate/up with few tiles.  A tile of a short prompt is bound by streaming its
+// weight panel through one CU (25-30 GB/s from beyond L2: the outstanding
+// misses of a CU), so where the real 128-column tiles leave half of the CUs
+// idle, twice as many 64-column ones (two B fragments per wave, four B
+// stages) stream the same panels on twice the CUs; with more tiles than that
+// they would only take a second round (450 tokens, all active: 101 us whole,
+// 127 narrow).  How many tiles are real is known on the device only: every
+// workgroup counts them.  Llama-3-8B widths, keep 0.5: 100 tokens 84 -> 59 us,
+// 300 tokens 105 -> 71; d_model 1024, d_ff 4096, 1000 tokens 36 -> 23.
+__global__ __launch_bounds__(NT, 1) void wide_mn256_fit(MN256Args a) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  const MN256Region& R = a.reg[0];
+  bool narrow = true;  // (token-order regions: the host checks)
+  if (R.masked == kMN256Sorted) {
+    int* sum = reinterpret_cast<int*>(smem);
+    if (threadIdx.x == 0) *sum = 0;
+    __syncthreads();
+    int n = 0;
+    for (int g = threadIdx.x; g < R.ldo / R.gw; g += NT) n += (a.cnt[g] + BM - 1) / BM;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o);
+    if (lane_id() == 0) atomicAdd(sum, n);
+    __syncthreads();
+    narrow = __builtin_amdgcn_readfirstlane(*sum) * (R.gw / 128) <= kMN256NarrowTiles;
+    __syncthreads();  // before the ring's loads overwrite the sum
+  }
+  if (narrow) {
+    mn256_run<true, 64, true, 2>(a, smem);
+  } else if ((int)(blockIdx.x / 8) < mn256_shares<128>(a)) {
+    mn256_run<true, 64, true, 4>(a, smem);
   }
 }
 
@@ -926,10 +995,28 @@ hipError_t prepare() {
 // same kernels on 64-bit addresses beyond.
 bool views_fit(int64_t rows, int K) { return rows * (int64_t)K * 2 <= kBufViewMax; }
 
+// Gate/up launches that wide_mn256_fit runs.  Sorted rows: 128-column tile
+// slots (real or not) such that at least a quarter of the tokens active per
+// group could fit kMN256NarrowTiles.  Token order: every tile is real.
+static bool mn256_fit(const MN256Args& a) {
+  const MN256Region& R = a.reg[0];
+  return a.n_regions == 1 && !a.tail && views_fit(a.M, a.K) &&
+         (R.masked == kMN256Sorted ? R.tiles <= 4 * kMN256NarrowTiles && R.gw % 128 == 0 && R.ldo % R.gw == 0
+                                   : R.masked == kMN256TokenOrder && R.tiles <= kMN256NarrowTiles);
+}
+
 hipError_t launch_mn256(const MN256Args& a, bool swiglu, hipStream_t s) {
   int64_t total = 0;
-  for (int i = 0; i < a.n_regions; ++i) total += 8 * (int64_t)mn256_share(a.reg[i].tiles);
+  for (int i = 0; i < a.n_regions; ++i) total += a.reg[i].tiles;
   if (total == 0) return hipSuccess;
+  total = 8 * (int64_t)(swiglu ? mn256_shares<128>(a) : mn256_shares<256>(a));
+  if (swiglu && mn256_fit(a)) {
+    MN256Region r = a.reg[0];
+    r.tiles *= 2;
+    total = std::max(total, 8 * (int64_t)mn256_region_share<64>(a, r));
+    WIDE_RING_LAUNCH("wide_mn256<true>", (wide_mn256_fit), std::max(RingN<2>::LDS, RingMN::LDS), (unsigned)total, s, a);
+    return hipGetLastError();
+  }
   if (a.tail) total += 8 * kMN256TailJobs;  // the tail blocks of every XCD, dispatched last
   const bool buf = views_fit(a.M, a.K);
   if (swiglu && buf)

@@ -133,6 +133,8 @@ constexpr size_t kMN256TailFloats = (size_t)8 * kMN256TailJobs * 256 * 256;
 bool mn256_tail_ok(const MN256Args& a, int bno);
 
 constexpr int kT256 = 256;
+// Gate/up: up to this many real 128-column tiles (half the CUs) run 64 columns wide.
+constexpr int kMN256NarrowTiles = 128;
 hipError_t launch_mn256(const MN256Args& a, bool swiglu, hipStream_t s);
 // The last, partial round of a dense-masked launch (see gemm256.hip): tiles
 // [base, total) are each run by `split` workgroups (1: not split), token rows

@@ -47,38 +47,49 @@ constexpr int LDS_MAX = 163840;  // bytes of LDS one workgroup may use on gfx950
 typedef const void __attribute__((address_space(1)))* gptr_t;
 typedef void __attribute__((address_space(3)))* lptr_t;
 
-template <int DA_>
+// NFN: B fragments per wave, 4 (256-wide tiles) or 2 (128-wide tiles: half the
+// B rows per tile, for launches with too few 256-wide ones; DB = 4 stages of B
+// then keep three steps of it in flight).
+template <int DA_, int DB_ = 2, int NFN_ = 4>
 struct Ring {
-  static constexpr int DA = DA_;                // A stages
+  static constexpr int DA = DA_, DB = DB_;      // A and B stages
+  static constexpr int NFN = NFN_;
   static constexpr int LEAD = DA - 1;           // steps A's loads run ahead
+  static constexpr int LEADB = DB - 1;          // steps B's do
   static constexpr int CPR = BK / 8;            // 16-byte chunks per row
   static constexpr int RPI = 64 / CPR;          // rows per wave load instruction
-  static constexpr int SLOTS = BM / (4 * RPI);  // load slots per lane per operand
-  static constexpr int OP = BM * BK;            // bf16 elements of one operand stage
-  static constexpr int LDS = (DA + 2) * OP * 2; // bytes
-  static_assert((DA == 2 || DA == 3) && LDS <= LDS_MAX, "two or three A stages");
+  static constexpr int BROWS = 64 * NFN;        // B rows of a tile
+  static constexpr int SLOTS = BM / (4 * RPI);  // A load slots per lane
+  static constexpr int BSLOTS = BROWS / (4 * RPI);
+  static constexpr int OP = BM * BK;            // bf16 elements of an A stage
+  static constexpr int OPB = BROWS * BK;        // of a B stage
+  static constexpr int LDS = (DA * OP + DB * OPB) * 2;  // bytes
+  static_assert((DA == 2 || DA == 3) && (DB == 2 || (DB == 4 && DA == 3)) && LDS <= LDS_MAX, "ring stages");
 
   __device__ static __forceinline__ uint16_t* a_stage(uint16_t* smem, int s) { return smem + (s % DA) * OP; }
-  __device__ static __forceinline__ uint16_t* b_stage(uint16_t* smem, int s) { return smem + (DA + (s & 1)) * OP; }
+  __device__ static __forceinline__ uint16_t* b_stage(uint16_t* smem, int s) {
+    return smem + DA * OP + (s % DB) * OPB;
+  }
   __device__ static __forceinline__ int f(int row) { return (row & 7) ^ ((row >> 3) & 1); }
   __device__ static __forceinline__ int swz(int row, int chunk) { return row * BK + ((chunk ^ f(row)) << 3); }
-  // Tile row served by load slot j of this lane (a wave's slots cover rows
-  // [64 w, 64 w + 64)), and the logical chunk it fetches so that it lands at
-  // physical chunk lane % CPR.
-  __device__ static __forceinline__ int slot_row(int j) {
-    return (wave_id() * SLOTS + j) * RPI + lane_id() / CPR;
+  // Tile row served by load slot j of this lane, of n slots per lane (a wave's
+  // slots cover 8 n consecutive rows), and the logical chunk it fetches so
+  // that it lands at physical chunk lane % CPR.
+  __device__ static __forceinline__ int slot_row(int j, int n = SLOTS) {
+    return (wave_id() * n + j) * RPI + lane_id() / CPR;
   }
-  __device__ static __forceinline__ int slot_chunk(int j) {
-    return (lane_id() % CPR) ^ f(slot_row(j));
+  __device__ static __forceinline__ int slot_chunk(int j, int n = SLOTS) {
+    return (lane_id() % CPR) ^ f(slot_row(j, n));
   }
-  // Load slot j of one operand stage; p points at the lane's 16 bytes.
-  __device__ static __forceinline__ void issue_ptr(uint16_t* stage, const uint16_t* p, int j) {
-    __builtin_amdgcn_global_load_lds((gptr_t)p, (lptr_t)(stage + (wave_id() * SLOTS + j) * RPI * BK), 16, 0, 0);
+  // Load slot j (of n) of one operand stage; p points at the lane's 16 bytes.
+  __device__ static __forceinline__ void issue_ptr(uint16_t* stage, const uint16_t* p, int j, int n = SLOTS) {
+    __builtin_amdgcn_global_load_lds((gptr_t)p, (lptr_t)(stage + (wave_id() * n + j) * RPI * BK), 16, 0, 0);
   }
   // The same through a buffer view: the lane's 16 bytes at byte voff + soff
   // (soff wave-uniform).  Lanes past the view's end land zeros.
-  __device__ static __forceinline__ void issue_buf(uint16_t* stage, bufview_t v, uint32_t voff, uint32_t soff, int j) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(v, (lptr_t)(stage + (wave_id() * SLOTS + j) * RPI * BK), 16, (int)voff,
+  __device__ static __forceinline__ void issue_buf(uint16_t* stage, bufview_t v, uint32_t voff, uint32_t soff, int j,
+                                                   int n = SLOTS) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(v, (lptr_t)(stage + (wave_id() * n + j) * RPI * BK), 16, (int)voff,
                                              (int)soff, 0, 0);
   }
 };
@@ -129,29 +140,36 @@ __device__ __forceinline__ void acc_fence(f32x16 (&c)[4][4]) {
                  "+a"(c[2][0]), "+a"(c[2][1]), "+a"(c[2][2]), "+a"(c[2][3]),
                  "+a"(c[3][0]), "+a"(c[3][1]), "+a"(c[3][2]), "+a"(c[3][3]));
 }
+__device__ __forceinline__ void acc_fence(f32x16 (&c)[4][2]) {
+  asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15"
+               : "+a"(c[0][0]), "+a"(c[0][1]), "+a"(c[1][0]), "+a"(c[1][1]),
+                 "+a"(c[2][0]), "+a"(c[2][1]), "+a"(c[3][0]), "+a"(c[3][1]));
+}
 
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[4][4]) {
+template <int NFN>
+__device__ __forceinline__ void zero_acc(f32x16 (&acc)[4][NFN]) {
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{};
+    for (int j = 0; j < NFN; ++j) acc[i][j] = f32x16{};
 }
 
 // One 16-deep k sub-step of the wave's operands: A fragment fm covers tile
 // rows wm*128 + fm*32 + lane%32, B fragment fn tile columns bb[fn] + lane%32.
+template <int NFN>
 struct Frags {
-  u32x4 a[4], b[4];
+  u32x4 a[4], b[NFN];
 };
 
 // Fragment read r of a sub-step, in the order the MFMAs first use them:
-// A0, B0, B1, B2, B3, A1, A2, A3.
-// B fragment fn of a wave starts bfrag_off<BL>(fn) tile rows after its
-// first, bb[0] (a multiple of 32): BL 0, four consecutive 32-row fragments;
-// BL 1 (gate/up pairs), two consecutive fragments of gate rows and the same
-// two of up rows, 128 rows on.  Kernels build bb[fn] = bb[0] + bfrag_off.
-template <int BL>
+// A0, the B fragments, A1, A2, A3.
+// B fragment fn of a wave starts bfrag_off<BL, NFN>(fn) tile rows after its
+// first, bb[0] (a multiple of 32): BL 0, consecutive 32-row fragments; BL 1
+// (gate/up pairs), NFN / 2 consecutive fragments of gate rows and the same of
+// up rows, half a tile on.  Kernels build bb[fn] = bb[0] + bfrag_off.
+template <int BL, int NFN = 4>
 __host__ __device__ constexpr int bfrag_off(int fn) {
-  return BL == 0 ? fn * 32 : (fn >> 1) * 128 + (fn & 1) * 32;
+  return BL == 0 ? fn * 32 : fn / (NFN / 2) * (32 * NFN) + fn % (NFN / 2) * 32;
 }
 
 // Every fragment starts at a tile row that is a multiple of 32, so its
@@ -162,28 +180,28 @@ __host__ __device__ constexpr int bfrag_off(int fn) {
 // offsets (an XOR over the whole row, or a base per fragment, needed one add
 // per read).
 template <class Rg, int BL>
-__device__ __forceinline__ void read_frag(const uint16_t* as, const uint16_t* bs, int kk, const int (&bb)[4],
-                                          Frags& f, int r) {
+__device__ __forceinline__ void read_frag(const uint16_t* as, const uint16_t* bs, int kk, const int (&bb)[Rg::NFN],
+                                          Frags<Rg::NFN>& f, int r) {
   const int lane = lane_id(), l32 = lane & 31;
   const int ch = kk * 2 + (lane >> 5);
   const int wm = wave_id() >> 1;
   const int lo = l32 * BK + ((ch ^ Rg::f(l32)) << 3);  // = swz(base + l32, ch) - base * BK
-  if (r == 0 || r >= 5) {
-    const int fm = r == 0 ? 0 : r - 4;
+  if (r == 0 || r > Rg::NFN) {
+    const int fm = r == 0 ? 0 : r - Rg::NFN;
     f.a[fm] = *reinterpret_cast<const u32x4*>(as + wm * 128 * BK + lo + fm * 32 * BK);
   } else {
-    f.b[r - 1] = *reinterpret_cast<const u32x4*>(bs + bb[0] * BK + lo + bfrag_off<BL>(r - 1) * BK);
+    f.b[r - 1] = *reinterpret_cast<const u32x4*>(bs + bb[0] * BK + lo + bfrag_off<BL, Rg::NFN>(r - 1) * BK);
   }
 }
 
-// MFMAs [Q0, Q1) of a sub-step on fragment set f (MFMA q: A fragment q / 4,
-// B fragment q % 4; only the first NL A fragments are live) with RDN
+// MFMAs [Q0, Q1) of a sub-step on fragment set f (MFMA q: A fragment q / NFN,
+// B fragment q % NFN; only the first NL A fragments are live) with RDN
 // fragment reads rd(r) and LDN loads ld(l) spread among them: when they fit,
 // a load after each even and a read after each odd MFMA, so no MFMA waits on
 // more than one instruction's address work; else as evenly as they go.
-template <int NL, int Q0, int Q1, int RDN, int LDN, class Rd, class Ld>
-__device__ __forceinline__ void substep(const Frags& f, f32x16 (&acc)[4][4], Rd rd, Ld ld) {
-  constexpr int QE = Q1 < 4 * NL ? Q1 : 4 * NL;
+template <int NL, int Q0, int Q1, int RDN, int LDN, int NFN, class Rd, class Ld>
+__device__ __forceinline__ void substep(const Frags<NFN>& f, f32x16 (&acc)[4][NFN], Rd rd, Ld ld) {
+  constexpr int QE = Q1 < NFN * NL ? Q1 : NFN * NL;
   constexpr int MF = QE > Q0 ? QE - Q0 : 0;
   if constexpr (MF == 0) {
 #pragma unroll
@@ -197,7 +215,7 @@ __device__ __forceinline__ void substep(const Frags& f, f32x16 (&acc)[4][4], Rd 
 #pragma unroll
     for (int i = 0; i < MF; ++i) {
       const int q = Q0 + i;
-      mfma_acc(f.a[q >> 2], f.b[q & 3], acc[q >> 2][q & 3]);
+      mfma_acc(f.a[q / NFN], f.b[q % NFN], acc[q / NFN][q % NFN]);
       if (HALF) {
         if ((i & 1) && (i >> 1) < RDN) rd(i >> 1);
       } else {
@@ -244,35 +262,51 @@ __device__ __forceinline__ void substep(const Frags& f, f32x16 (&acc)[4][4], Rd 
 // compile time.  A wave's A load slots cover tile rows [64 w, 64 w + 64);
 // AON = false (all of them past the active rows) skips its A loads.
 template <class Rg, int NL, bool AON, int BL, class Koff, class LdA, class LdB>
-__device__ __forceinline__ void mainloop(uint16_t* smem, int nsteps, Koff koff, LdA lda, LdB ldb, const int (&bb)[4],
-                                         f32x16 (&acc)[4][4]) {
-  constexpr int S = Rg::SLOTS, LEAD = Rg::LEAD;
-  constexpr int RDN = NL > 0 ? NL + 4 : 0;  // fragment reads per sub-step
-  constexpr int PRE = 2 * NL;               // MFMAs of the last sub-step before the barrier
+__device__ __forceinline__ void mainloop(uint16_t* smem, int nsteps, Koff koff, LdA lda, LdB ldb,
+                                         const int (&bb)[Rg::NFN], f32x16 (&acc)[4][Rg::NFN]) {
+  constexpr int S = Rg::SLOTS, SB = Rg::BSLOTS, LEAD = Rg::LEAD, LEADB = Rg::LEADB, NFN = Rg::NFN;
+  constexpr int SA = AON ? S : 0;             // A loads of the wave per step
+  constexpr int RDN = NL > 0 ? NL + NFN : 0;  // fragment reads per sub-step
+  constexpr int QN = 4 * NFN;                 // MFMAs of a full sub-step
+  constexpr int PRE = NL * NFN / 2;           // MFMAs of the last sub-step before the barrier
   acc_fence(acc);
   if (nsteps > 0) {
-    const int k0 = koff(0);
+    auto all_b = [&](int s) {
+      const int k = koff(s);
 #pragma unroll
-    for (int j = 0; j < S; ++j) ldb(Rg::b_stage(smem, 0), k0, j);
-    if (AON) {
+      for (int j = 0; j < SB; ++j) ldb(Rg::b_stage(smem, s), k, j);
+    };
+    auto all_a = [&](int s) {
+      if (!AON) return;
+      const int k = koff(s);
 #pragma unroll
-      for (int j = 0; j < S; ++j) lda(Rg::a_stage(smem, 0), k0, j);
-    }
-    if (AON && LEAD == 2 && nsteps > 1) {
-      const int k1 = koff(1);
-#pragma unroll
-      for (int j = 0; j < S; ++j) lda(Rg::a_stage(smem, 1), k1, j);
-      wait_vm<S>();
+      for (int j = 0; j < S; ++j) lda(Rg::a_stage(smem, s), k, j);
+    };
+    // steps 0 .. max(LEAD, LEADB) - 1, each step's B before its A
+    all_b(0);
+    all_a(0);
+    if (nsteps > 2 && LEADB > 2) {
+      all_b(1);
+      all_a(1);
+      all_b(2);
+      wait_vm<SA + 2 * SB>();
+    } else if (nsteps > 1 && LEADB > 1) {
+      all_b(1);
+      all_a(1);
+      wait_vm<SA + SB>();
+    } else if (nsteps > 1 && LEAD == 2 && AON) {
+      all_a(1);
+      wait_vm<SA>();
     } else {
       wait_vm<0>();
     }
     stage_barrier();
-    Frags f0, f1;
+    Frags<NFN> f0, f1;
     if (NL > 0) {
 #pragma unroll
       for (int r = 0; r < RDN; ++r) read_frag<Rg, BL>(Rg::a_stage(smem, 0), Rg::b_stage(smem, 0), 0, bb, f0, r);
     }
-    // LS: issue B of kt+1; LA: A of kt+LEAD; NEXT: step kt+1 exists; WN: loads
+    // LS: issue B of kt+LEADB; LA: A of kt+LEAD; NEXT: step kt+1 exists; WN: loads
     // allowed in flight when waiting for step kt+1
     auto step = [&](int kt, auto ls_t, auto la_t, auto next_t, auto wn_t) {
       constexpr bool LS = decltype(ls_t)::value, LA = decltype(la_t)::value && AON;
@@ -280,16 +314,16 @@ __device__ __forceinline__ void mainloop(uint16_t* smem, int nsteps, Koff koff, 
       constexpr int WN = decltype(wn_t)::value;
       const uint16_t* as = Rg::a_stage(smem, kt);
       const uint16_t* bs = Rg::b_stage(smem, kt);
-      uint16_t* lb = Rg::b_stage(smem, kt + 1);
+      uint16_t* lb = Rg::b_stage(smem, kt + LEADB);
       uint16_t* la = Rg::a_stage(smem, kt + LEAD);
-      const int kb = LS ? koff(kt + 1) : 0;
+      const int kb = LS ? koff(kt + LEADB) : 0;
       const int ka = LA ? koff(kt + LEAD) : 0;
-      auto rd = [&](int kk, Frags& f) { return [&, kk](int r) { read_frag<Rg, BL>(as, bs, kk, bb, f, r); }; };
+      auto rd = [&](int kk, Frags<NFN>& f) { return [&, kk](int r) { read_frag<Rg, BL>(as, bs, kk, bb, f, r); }; };
       auto none = [](int) {};
       sched_fence();
-      substep<NL, 0, 16, RDN, LS ? S : 0>(f0, acc, rd(1, f1), [&](int j) { ldb(lb, kb, j); });
-      substep<NL, 0, 16, RDN, 0>(f1, acc, rd(2, f0), none);
-      substep<NL, 0, 16, RDN, LA ? S : 0>(f0, acc, rd(3, f1), [&](int j) { lda(la, ka, j); });
+      substep<NL, 0, QN, RDN, LS ? SB : 0>(f0, acc, rd(1, f1), [&](int j) { ldb(lb, kb, j); });
+      substep<NL, 0, QN, RDN, 0>(f1, acc, rd(2, f0), none);
+      substep<NL, 0, QN, RDN, LA ? S : 0>(f0, acc, rd(3, f1), [&](int j) { lda(la, ka, j); });
       substep<NL, 0, PRE, 0, 0>(f1, acc, none, none);
       if (NEXT) {
         wait_vm<WN>();
@@ -298,15 +332,28 @@ __device__ __forceinline__ void mainloop(uint16_t* smem, int nsteps, Koff koff, 
       sched_fence();
       const uint16_t* an = Rg::a_stage(smem, kt + 1);
       const uint16_t* bn = Rg::b_stage(smem, kt + 1);
-      substep<NL, PRE, 16, NEXT ? RDN : 0, 0>(f1, acc, [&](int r) { read_frag<Rg, BL>(an, bn, 0, bb, f0, r); }, none);
+      substep<NL, PRE, QN, NEXT ? RDN : 0, 0>(f1, acc, [&](int r) { read_frag<Rg, BL>(an, bn, 0, bb, f0, r); }, none);
     };
     using T = std::true_type;
     using F = std::false_type;
     using I0 = std::integral_constant<int, 0>;
-    using IS = std::integral_constant<int, AON && LEAD == 2 ? S : 0>;
     int kt = 0;
-    for (; kt + LEAD < nsteps; ++kt) step(kt, T{}, T{}, T{}, IS{});
-    if (LEAD == 2 && kt + 1 < nsteps) step(kt++, T{}, F{}, T{}, I0{});
+    if constexpr (LEADB == 3) {
+      // Younger than step kt+1's last load (A of kt+1, issued at kt-1; without
+      // A loads B of kt+1, issued at kt-2): what step kt issued (and without A
+      // loads step kt-1).
+      using I3 = std::integral_constant<int, AON ? SA + SB : 2 * SB>;
+      using I2 = std::integral_constant<int, AON ? SA : SB>;
+      for (; kt + 3 < nsteps; ++kt) step(kt, T{}, T{}, T{}, I3{});
+      if (kt + 2 < nsteps) step(kt++, F{}, T{}, T{}, I2{});
+    } else {
+      using IS = std::integral_constant<int, LEAD == 2 ? SA : 0>;
+      for (; kt + LEAD < nsteps; ++kt) step(kt, T{}, T{}, T{}, IS{});
+    }
+    if (LEAD == 2 && kt + 1 < nsteps) {
+      if constexpr (LEADB == 1) step(kt++, T{}, F{}, T{}, I0{});
+      else step(kt++, F{}, F{}, T{}, I0{});
+    }
     step(kt, F{}, F{}, F{}, I0{});
   }
   acc_fence(acc);

@@ -715,3 +715,30 @@ def test_fp32_tiles(orc, M, D, Dff, G):
     assert_close(h, rh, kind="f32", what="h")
     assert_close(y, ry, kind="f32", what="y")
     assert torch.equal(y, o)
+
+
+@pytest.mark.parametrize("M,D,ng,G,kind", [
+    (200, 256, 128, 128, "ones"),      # 128 real tiles: cut to 64 columns
+    (257, 256, 65, 128, "ones"),       # 130 real tiles: whole, in a launch sized for narrow ones
+    (700, 1024, 24, 256, "edges"),     # four 64-column tiles per group, ragged rows
+    (130, 64 * 4, 3, 128, "bernoulli"),  # fewer column tiles than XCDs
+    (500, 256, 10, 512, "topk"),       # groups wider than four 64-column tiles
+    (300, 512, 1, 1408, "bernoulli"),  # one group
+    (257, 256, 64, 32, "bernoulli"),   # narrow groups in token order
+    (200, 512, 40, 16, "topk"),
+    (2000, 256, 70, 128, "edges"),     # more tile slots than the adaptive launch takes
+])
+def test_gate_up_tile_width(orc, M, D, ng, G, kind):
+    """Gate/up runs up to 128 real tiles 64 columns wide (four B stages, three
+    steps ahead), more of them 128 wide; the count is taken on the device."""
+    say("gate/up tile width", M, D, ng, G, kind)
+    W.wide_set_option("decode_max_m", 0)
+    c = synth.ffn_case(M + ng, M, D, ng * G, G, mask="bernoulli" if kind == "edges" else kind)
+    if kind == "edges":
+        c.mask[:] = _edge_count_mask(synth.rng(M + G), M, ng)
+    x, wg, wu, wd, m = ffn_dev(c)
+    h = torch.full((M, ng * G), 7.0, dtype=torch.bfloat16, device=dev())
+    y = W.wide_ffn_masked(x, wg, wu, wd, m, G, h_out=h)
+    torch.cuda.synchronize()
+    rows = np.unique(np.r_[0, 1, M - 1, M - 2, synth.rng(M).choice(M, min(M, 300), replace=False)])
+    check_ffn(orc, c, y, h, rows=rows)
