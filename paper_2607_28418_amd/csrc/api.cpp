@@ -782,7 +782,8 @@ wide_status_t ffn_masked(wide_dtype_t dt, int64_t M, int32_t d_model, int32_t d_
     ix = r.idx;
     ct = r.cnt;
   }
-  if (g_big_tiles && G % 128 == 0) {
+  const bool half = G == 64 && g_big_tiles && wide::mn256_half_ok(M, D);
+  if (g_big_tiles && (G % 128 == 0 || half)) {
     wide::MN256Args ma{};
     ma.order = (g_mn_order >> 1) & 1;
     ma.mblock = (g_mn_order >> 2) & 1;
@@ -796,10 +797,11 @@ wide_status_t ffn_masked(wide_dtype_t dt, int64_t M, int32_t d_model, int32_t d_
     // An H kept in the workspace is read only through its active blocks by
     // every K-axis schedule, so its inactive blocks need no zeros.
     ma.reg[0] = wide::MN256Region{static_cast<const uint16_t*>(w_gate), static_cast<const uint16_t*>(w_up), h,
-                                  Dff, G, 1, ng * ma.m_tiles * (G / 128), h_out == nullptr ? 1 : 0};
+                                  Dff, G, 1, ng * ma.m_tiles * (half ? 1 : G / 128), h_out == nullptr ? 1 : 0};
     // (no tail split for gate/up: over seven rounds of tiles the chunks and
     // their finishing kernel cost about what the last partial round saves)
-    if ((e = wide::launch_mn256(ma, true, stream)) != hipSuccess) return hip_fail(e, "mn256 gate/up");
+    e = half ? wide::launch_mn256_half(ma, true, stream) : wide::launch_mn256(ma, true, stream);
+    if (e != hipSuccess) return hip_fail(e, "mn256 gate/up");
   } else {
     wide::MNArgs ma{};
     ma.x = static_cast<const uint16_t*>(x);
@@ -1020,6 +1022,28 @@ wide_status_t wide_qkvo_masked(wide_phase_t phase, wide_dtype_t dt, int64_t M, i
       ma.tail = g_mn_tail && wide::mn256_tail_ok(ma, 256) ? 1 : 0;
       ma.tail_ws = tail_ws;
       if ((e = wide::launch_mn256(ma, false, stream)) != hipSuccess) return hip_fail(e, "mn256 qkv");
+      return ok();
+    }
+    // Groups of an odd number of 128 columns, or K and V widths no multiple of
+    // 256: 256 x 128 tiles (G <= 512: the tile order's groups), else 128 x 128.
+    if (g_big_tiles && d.G <= 512 && wide::mn256_half_ok(M, d.D)) {
+      wide::MN256Args ha{};
+      ha.order = (g_mn_order >> 1) & 1;
+      ha.x = x;
+      ha.M = M;
+      ha.K = d.D;
+      ha.idx = ix;
+      ha.cnt = ct;
+      ha.m_tiles = (int)((M + wide::kT256 - 1) / wide::kT256);
+      ha.n_regions = 3;
+      const int iq = (g_mn_order & 1) ? 2 : 0, ik = iq ? 0 : 1;  // K and V first, as above
+      ha.reg[ik] = wide::MN256Region{wk, nullptr, static_cast<uint16_t*>(k), d.Nkv, d.Nkv, 0,
+                                     ha.m_tiles * (d.Nkv / 128)};
+      ha.reg[ik + 1] = wide::MN256Region{wv, nullptr, static_cast<uint16_t*>(v), d.Nkv, d.Nkv, 0,
+                                         ha.m_tiles * (d.Nkv / 128)};
+      ha.reg[iq] = wide::MN256Region{wq, nullptr, static_cast<uint16_t*>(q), d.Nq, d.G, wide::kMN256Sorted,
+                                     ng * ha.m_tiles * (d.G / 128)};
+      if ((e = wide::launch_mn256_half(ha, false, stream)) != hipSuccess) return hip_fail(e, "mn256 qkv");
       return ok();
     }
     wide::MNArgs ma{};

@@ -302,9 +302,10 @@ __device__ __forceinline__ void mn256_chunk_steps(int K, int c, int n, int& s0, 
 }
 
 // --------------------------------------------------------------------- GEMM-MN
-// NFN = 2 (gate/up only): tiles of 128 weight rows, 64 output columns (see
-// wide_mn256_fit).
-template <bool SWIGLU, int BK, bool BUF, int NFN>
+// NFN = 2: tiles of 128 weight rows (64 gate/up columns or 128 plain ones), for
+// narrow groups (wide_mn256_half) and few tiles (wide_mn256_fit).
+// DOUBLE: the region's tiles are counted in 128-column ones (one region).
+template <bool SWIGLU, int BK, bool BUF, int NFN, bool DOUBLE = false>
 __device__ __forceinline__ void mn256_run(const MN256Args& a, uint16_t* smem) {
   static_assert(BK == t256::BK, "64-deep ring");
   using Rg = RingN<NFN>;
@@ -323,8 +324,7 @@ __device__ __forceinline__ void mn256_run(const MN256Args& a, uint16_t* smem) {
   int local = blockIdx.x / 8;
   int ri = 0, job = -1;   // region; tail job of a tail block
   int chunk = 0, nchunks = 1;
-  if (NFN == 2) {  // one region, no tail
-  } else if (const int shares = mn256_shares<BNO>(a); local >= shares) {  // one of the 32 tail blocks per XCD
+  if (const int shares = mn256_shares<BNO>(a); NFN == 4 && local >= shares) {  // one of the 32 tail blocks per XCD
     job = local - shares;
     const MN256Tail t = mn256_tail<BNO>(a, xcd);
     if (job >= t.n * t.split) return;
@@ -349,7 +349,7 @@ __device__ __forceinline__ void mn256_run(const MN256Args& a, uint16_t* smem) {
     }
   }
   MN256Region R = ri == 0 ? a.reg[0] : ri == 1 ? a.reg[1] : a.reg[2];
-  if (NFN == 2) R.tiles *= 2;
+  if (DOUBLE) R.tiles *= 2;
   if (!mn256_mblocked<BNO>(a, R) && xcd * mn256_share(R.tiles) + local >= R.tiles) return;  // padding
   int g, nt_in, m_tile;
   mn256_coords<BNO>(a, R, xcd, local, g, m_tile, nt_in);
@@ -459,6 +459,7 @@ __device__ __forceinline__ void mn256_run(const MN256Args& a, uint16_t* smem) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int r = acc_row(fm, i);
+        if (m0 + r >= cnt) continue;  // the finishing kernel does not read rows past the active ones
 #pragma unroll
         for (int fn = 0; fn < NFN; ++fn) P[r * BN + bb[fn] + col] = acc[fm][fn][i];
       }
@@ -510,6 +511,18 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256(MN256Args a) {
   mn256_run<SWIGLU, BK, BUF, 4>(a, smem);
 }
 
+// Groups of half a tile: gate/up groups of 64 channels, Q groups of 128
+// columns (K and V then run 128-wide too).  These ran on the 128 x 128 kernel
+// of gemm_mn.hip (operands staged through registers, half the MFMAs per loaded
+// byte).  Llama-3-8B widths, groups of 64: gate/up at 1000 tokens and keep 0.25
+// 212 -> 110 us, at 4096 and 0.75 1131 -> 696; Q/K/V in groups of 128 at 777
+// tokens 93 -> 55 us, at 8192 566 -> 365.
+template <bool SWIGLU>
+__global__ __launch_bounds__(NT, 1) void wide_mn256_half(MN256Args a) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  mn256_run<SWIGLU, 64, true, 2>(a, smem);
+}
+
 // Gate/up with few tiles.  A tile of a short prompt is bound by streaming its
 // weight panel through one CU (25-30 GB/s from beyond L2: the outstanding
 // misses of a CU), so where the real 128-column tiles leave half of the CUs
@@ -537,7 +550,7 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256_fit(MN256Args a) {
     __syncthreads();  // before the ring's loads overwrite the sum
   }
   if (narrow) {
-    mn256_run<true, 64, true, 2>(a, smem);
+    mn256_run<true, 64, true, 2, true>(a, smem);
   } else if ((int)(blockIdx.x / 8) < mn256_shares<128>(a)) {
     mn256_run<true, 64, true, 4>(a, smem);
   }
@@ -545,19 +558,23 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256_fit(MN256Args a) {
 
 // Finish the XCDs' tail tiles: add each tile's chunks in order, then the
 // mn256 epilogue (SwiGLU or plain, rows back to token order).  Workgroup
-// (xcd, k, rb) takes rows [16 rb, 16 rb + 16) of tail tile k; each thread
-// loads the chunks of its elements together (independent loads) and adds
-// them in chunk order.
-constexpr int kTailRows = 16;
+// (xcd, k, rb) takes kTailRows rows of tail tile k; each thread
+// loads the chunks of its elements together (independent 16-byte loads) and adds
+// them in chunk order.  Bound by the partial tiles' bytes per CU, so rows past
+// the active ones are neither written nor read and a workgroup takes few rows
+// (Llama-3-8B, 100 tokens: 20 us with 16 rows and 4-byte loads, now 12; 4 rows
+// 14).
+constexpr int kTailRows = 8;
+constexpr int kTailTiles = kMN256TailJobs / 2;  // at most: two chunks each
 template <bool SWIGLU>
 __global__ __launch_bounds__(NT) void wide_mn256_tail(MN256Args a) {
   constexpr int BNO = SWIGLU ? 128 : 256;
-  constexpr int PER = kTailRows * BNO / NT;  // elements per thread
+  constexpr int PER = kTailRows * BNO / NT / 4;  // runs of four columns per thread
   __shared__ int map[kTailRows];
   static_assert(kTailRows <= NT, "one thread per row for the row map");
   const int rb = blockIdx.x % (BM / kTailRows);
-  const int k = (blockIdx.x / (BM / kTailRows)) % kMN256TailJobs;
-  const int xcd = blockIdx.x / (BM / kTailRows * kMN256TailJobs);
+  const int k = (blockIdx.x / (BM / kTailRows)) % kTailTiles;
+  const int xcd = blockIdx.x / (BM / kTailRows * kTailTiles);
   const MN256Tail t = mn256_tail<BNO>(a, xcd);
   if (k >= t.n) return;
   int ri, local, g, m_tile, nt_in;
@@ -565,35 +582,42 @@ __global__ __launch_bounds__(NT) void wide_mn256_tail(MN256Args a) {
   const MN256Region R = ri == 0 ? a.reg[0] : ri == 1 ? a.reg[1] : a.reg[2];
   mn256_coords<BNO>(a, R, xcd, local, g, m_tile, nt_in);
   const int n0 = g * R.gw + nt_in * BNO;
-  const int32_t* rows = R.masked ? a.idx + (int64_t)g * a.M : nullptr;
+  const int32_t* rows = R.masked == kMN256Sorted ? a.idx + (int64_t)g * a.M : nullptr;
+  const int64_t cnt = R.masked == kMN256Sorted ? (int64_t)a.cnt[g] : a.M;
   const int64_t p0 = (int64_t)m_tile * BM + rb * kTailRows;
   const int tid = threadIdx.x;
   if (tid < kTailRows) map[tid] = p0 + tid < a.M ? (rows ? rows[p0 + tid] : (int)(p0 + tid)) : -1;
   __syncthreads();
   const float* P = a.tail_ws + ((int64_t)xcd * kMN256TailJobs + k * t.split) * (BM * BN);
 #pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const int i = e * NT + tid;
+  for (int e = 0; e < PER; ++e) {  // four columns at a time
+    const int i = (e * NT + tid) * 4;
     const int r = i / BNO, c = i % BNO;
     const int tok = map[r];
+    if (tok < 0) continue;
+    const bool live = p0 + r < cnt;  // past the active rows: +0, nothing was written
     const float* Pe = P + (rb * kTailRows + r) * BN + c;
-    float v0[kMN256TailMaxSplit], v1[kMN256TailMaxSplit];
+    f32x4 v0[kMN256TailMaxSplit], v1[kMN256TailMaxSplit];
 #pragma unroll
     for (int q = 0; q < kMN256TailMaxSplit; ++q) {
-      const bool on = q < t.split;
-      const float* Pq = Pe + (int64_t)(on ? q : 0) * (BM * BN);  // in range whether or not used
-      v0[q] = on ? Pq[0] : 0.f;
-      v1[q] = SWIGLU && on ? Pq[128] : 0.f;
+      const bool on = live && q < t.split;
+      const float* Pq = Pe + (int64_t)(on ? q : 0) * (BM * BN);
+      v0[q] = on ? *reinterpret_cast<const f32x4*>(Pq) : f32x4{0.f, 0.f, 0.f, 0.f};
+      v1[q] = SWIGLU && on ? *reinterpret_cast<const f32x4*>(Pq + 128) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    float s0 = 0.f, s1 = 0.f;
+    f32x4 s0{0.f, 0.f, 0.f, 0.f}, s1{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int q = 0; q < kMN256TailMaxSplit; ++q) {  // chunk order
       s0 += v0[q];
       s1 += v1[q];
     }
-    if (tok < 0) continue;
-    const bool on = R.masked != kMN256TokenOrder || a.mask[(int64_t)tok * a.mask_ng + (n0 + c) / a.mask_G] != 0;
-    R.out[(int64_t)tok * R.ldo + n0 + c] = f32_to_bf16_hw(on ? (SWIGLU ? silu(s0) * s1 : s0) : 0.f);
+    // (token-order groups are at least 16 columns wide, so the four share one)
+    const bool on = live && (R.masked != kMN256TokenOrder || a.mask[(int64_t)tok * a.mask_ng + (n0 + c) / a.mask_G] != 0);
+    float o[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = on ? (SWIGLU ? silu(s0[j]) * s1[j] : s0[j]) : 0.f;
+    *reinterpret_cast<uint2*>(R.out + (int64_t)tok * R.ldo + n0 + c) =
+        uint2{pack_bf16x2_hw(o[0], o[1]), pack_bf16x2_hw(o[2], o[3])};
   }
 }
 
@@ -1005,6 +1029,19 @@ static bool mn256_fit(const MN256Args& a) {
                                    : R.masked == kMN256TokenOrder && R.tiles <= kMN256NarrowTiles);
 }
 
+bool mn256_half_ok(int64_t M, int K) { return views_fit(M, K); }
+
+hipError_t launch_mn256_half(const MN256Args& a, bool swiglu, hipStream_t s) {
+  const int64_t total = 8 * (int64_t)(swiglu ? mn256_shares<64>(a) : mn256_shares<128>(a));
+  if (total == 0) return hipSuccess;
+  if (!views_fit(a.M, a.K) || a.tail) return hipErrorInvalidValue;
+  if (swiglu)
+    WIDE_RING_LAUNCH("wide_mn256_half<true>", (wide_mn256_half<true>), RingN<2>::LDS, (unsigned)total, s, a);
+  else
+    WIDE_RING_LAUNCH("wide_mn256_half<false>", (wide_mn256_half<false>), RingN<2>::LDS, (unsigned)total, s, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_mn256(const MN256Args& a, bool swiglu, hipStream_t s) {
   int64_t total = 0;
   for (int i = 0; i < a.n_regions; ++i) total += a.reg[i].tiles;
@@ -1029,7 +1066,7 @@ hipError_t launch_mn256(const MN256Args& a, bool swiglu, hipStream_t s) {
     WIDE_RING_LAUNCH("wide_mn256<false>", (wide_mn256<false, 64, false>), RingMN::LDS, (unsigned)total, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !a.tail) return e;
-  const dim3 tg(8 * kMN256TailJobs * (BM / kTailRows));
+  const dim3 tg(8 * kTailTiles * (BM / kTailRows));
   if (swiglu)
     WIDE_LAUNCH(wide_mn256_tail<true>, tg, dim3(NT), 0, s, a);
   else

@@ -742,3 +742,30 @@ def test_gate_up_tile_width(orc, M, D, ng, G, kind):
     torch.cuda.synchronize()
     rows = np.unique(np.r_[0, 1, M - 1, M - 2, synth.rng(M).choice(M, min(M, 300), replace=False)])
     check_ffn(orc, c, y, h, rows=rows)
+
+
+@pytest.mark.parametrize("M,n_q,n_kv,G", [
+    (300, 8, 2, 128),     # one 128-column tile per group
+    (520, 6, 1, 256),     # K and V of 128 columns
+    (257, 6, 2, 384),     # three tiles per group, group counts that do not divide among the XCDs
+    (100, 16, 4, 512),    # 256-wide tiles, each XCD's few tiles cut along k, many dead rows
+])
+def test_qkv_half_tiles(orc, M, n_q, n_kv, G):
+    say("qkv half tiles", M, n_q, n_kv, G)
+    c = synth.attn_case(M + G, M, 512, n_q, n_kv, 128, G, mask="bernoulli")
+    check_qkvo(orc, c)
+
+
+def test_qkv_token_order_ignores_a_given_reorder(orc):
+    """Groups of 64 run in token order; the finishing kernel of the tiles cut
+    along k must not follow the caller's reorder there."""
+    say("qkv token order, reorder given")
+    c = synth.attn_case(5, 300, 512, 8, 4, 64, 64, mask="bernoulli")
+    d = attn_dev(c)
+    idx, counts = W.wide_mask_reorder(d["mask"])
+    q, k, v = W.wide_qkvo_masked(W.PHASE_QKV, d["x"], d["mask"], 64, 8, 4, 64, w_q=d["w_q"], w_k=d["w_k"],
+                                 w_v=d["w_v"], idx=idx, counts=counts)
+    torch.cuda.synchronize()
+    check_nproj(orc, c.x, c.w_q, c.mask, 64, q, what="q")
+    check_nproj(orc, c.x, c.w_k, None, 0, k, what="k")
+    check_nproj(orc, c.x, c.w_v, None, 0, v, what="v")
