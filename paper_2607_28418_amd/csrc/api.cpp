@@ -676,14 +676,20 @@ wide_status_t wide_router(wide_dtype_t dt, int64_t M, int32_t d_model, int32_t r
     CHECK(check_ws(ws, ws_bytes, c0.off));
   }
   wide::RouterArgs ra{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w1),
-                      static_cast<const uint16_t*>(w2), mask, logits, M, d_model, rank, n_groups};
+                      static_cast<const uint16_t*>(w2), mask, logits, M, d_model, rank, n_groups, nullptr, 0};
+  Carve c(ws);
+  ReorderWS r;
+  const bool by_bits = idx && M <= wide::kReorderBitsMax;
+  if (idx) carve_reorder(c, M, n_groups, false, r);
+  if (by_bits) {  // the reorder's two scratch arrays, back to back, hold the mask's bits
+    ra.bits = reinterpret_cast<uint32_t*>(r.chunk_cnt);
+    ra.bits_ld = (int)((M + 31) / 32);
+  }
   hipError_t e = wide::launch_router(ra, stream);
   if (e != hipSuccess) return hip_fail(e, "router");
   if (idx) {
-    Carve c(ws);
-    ReorderWS r;
-    carve_reorder(c, M, n_groups, false, r);
-    e = wide::launch_reorder(mask, M, n_groups, idx, counts, r.chunk_cnt, r.chunk_off, stream);
+    e = by_bits ? wide::launch_reorder_bits(ra.bits, (int)M, n_groups, idx, counts, stream)
+                : wide::launch_reorder(mask, M, n_groups, idx, counts, r.chunk_cnt, r.chunk_off, stream);
     if (e != hipSuccess) return hip_fail(e, "router reorder");
   }
   return ok();

@@ -14,6 +14,11 @@ hipError_t launch_reorder(const uint8_t* mask, int64_t M, int n_groups,
                           int32_t* idx, int32_t* counts, int32_t* chunk_cnt,
                           int32_t* chunk_off, hipStream_t s);
 size_t reorder_scratch_ints(int64_t M, int n_groups);
+// The same from the mask's bits (RouterArgs::bits), up to kReorderBitsMax
+// tokens; the bits of M tokens fit the two scratch arrays of launch_reorder.
+constexpr int kReorderBitsMax = 32768;
+hipError_t launch_reorder_bits(const uint32_t* bits, int M, int n_groups, int32_t* idx, int32_t* counts,
+                               hipStream_t s);
 // Token order by mask pattern (n_groups <= 8): perm[M] lists the tokens
 // grouped by their mask row.  scratch: pattern_scratch_ints(M) ints.
 constexpr int kPatternMaxGroups = 8;
@@ -215,6 +220,8 @@ struct RouterArgs {
   float* logits;       // optional [M][2 ng] out
   int64_t M;
   int D, r, ng;        // D % 64 == 0, 1 <= r <= 32
+  uint32_t* bits;      // optional [ng][bits_ld] out: bit t % 32 of word t / 32 is mask[t][g]
+  int bits_ld;         // ceil(M / 32)
 };
 hipError_t launch_router(const RouterArgs& a, hipStream_t s);
 

@@ -41,6 +41,10 @@ static_assert(kRW * kRTok * kRPad * 4 <= kRNst * 2 * kRTileB, "partials fit in t
 static_assert(2 * (kRT / 8) * kRPad * 4 <= kRNst * 2 * kRTileB, "W2 rows fit in the ring");
 }  // namespace
 
+// RP: bottleneck units carried (16 or 32, at least the rank).  Units past it
+// would only add exact zeros, so both widths give the same bits; at rank 16 the
+// narrow one loads half of W1 and does half of stage 2.
+template <int RP>
 __global__ __launch_bounds__(kRT) void wide_router(RouterArgs a) {
   // The ring; after stage 1 the same bytes hold the waves' partials, then
   // stage 2's W2 rows.
@@ -57,8 +61,9 @@ __global__ __launch_bounds__(kRT) void wide_router(RouterArgs a) {
   // 16-byte pieces, piece j at position j ^ (row % 32) so that the operand
   // reads (32 rows, one piece each) spread over the banks.  Wave w loads rows
   // 2w and 2w+1 of both operands: lane l writes position l % 32 of row
-  // 2w + l / 32 and so fetches piece (l % 32) ^ row.  Every wave issues its
-  // two loads for every chunk (uniform wait counts): token rows past M read
+  // 2w + l / 32 and so fetches piece (l % 32) ^ row; waves whose W1 rows lie
+  // past RP load X only.  Every wave issues the same loads for every chunk (a
+  // fixed wait count per wave): token rows past M read
   // the last token, units past the rank the last unit (never used: H's
   // columns past the rank are zeroed below), pieces past d_model the row's
   // first piece (no wave reads them).
@@ -68,12 +73,13 @@ __global__ __launch_bounds__(kRT) void wide_router(RouterArgs a) {
   const char* xrow = reinterpret_cast<const char*>(a.x + (t0 + min(lrow, rows - 1)) * (int64_t)D);
   const char* wrow = reinterpret_cast<const char*>(a.w1 + (int64_t)min(lrow, r - 1) * D);
   const int nch = (D + kRChunk - 1) / kRChunk;
+  const bool has_w = RP == 32 || 2 * w < RP;
   auto issue = [&](int c) {
     const int st = c % kRNst;
     const int64_t off = (int64_t)c * kRRowB + (c * kRChunk + piece * 8 < D ? piece * 16 : 0);
     char* xs = s_ring + st * 2 * kRTileB + 2 * w * kRRowB;
     __builtin_amdgcn_global_load_lds((t256::gptr_t)(xrow + off), (t256::lptr_t)xs, 16, 0, 0);
-    __builtin_amdgcn_global_load_lds((t256::gptr_t)(wrow + off), (t256::lptr_t)(xs + kRTileB), 16, 0, 0);
+    if (has_w) __builtin_amdgcn_global_load_lds((t256::gptr_t)(wrow + off), (t256::lptr_t)(xs + kRTileB), 16, 0, 0);
   };
   // This wave's k step in each chunk: pieces 2w (lane half 0) and 2w + 1.
   const int rd = l32 * kRRowB + (((2 * w + lhi) ^ l32) << 4);
@@ -81,8 +87,9 @@ __global__ __launch_bounds__(kRT) void wide_router(RouterArgs a) {
   for (int c = 0; c < min(kRNst - 1, nch); ++c) issue(c);
   for (int c = 0; c < nch; ++c) {
     const int younger = min(kRNst - 2, nch - 1 - c);  // chunks issued after c
-    if (younger >= 2) t256::wait_vm<4>();
-    else if (younger == 1) t256::wait_vm<2>();
+    if (younger >= 2 && has_w) t256::wait_vm<4>();
+    else if (younger >= 2 || (younger == 1 && has_w)) t256::wait_vm<2>();
+    else if (younger == 1) t256::wait_vm<1>();
     else t256::wait_vm<0>();
     t256::stage_barrier();  // chunk c is in LDS; every wave is done with chunk c - 1
     if (c + kRNst - 1 < nch) issue(c + kRNst - 1);
@@ -98,8 +105,8 @@ __global__ __launch_bounds__(kRT) void wide_router(RouterArgs a) {
 #pragma unroll
   for (int i = 0; i < 16; ++i) s_part[w][(i >> 2) * 8 + lhi * 4 + (i & 3)][l32] = acc[i];
   __syncthreads();
-  for (int i = tid; i < kRTok * kRouterMaxRank; i += kRT) {
-    const int t = i / kRouterMaxRank, u = i % kRouterMaxRank;
+  for (int i = tid; i < kRTok * RP; i += kRT) {
+    const int t = i / RP, u = i % RP;
     float s = 0.f;
 #pragma unroll
     for (int q = 0; q < kRW; ++q) s += s_part[q][t][u];
@@ -115,8 +122,19 @@ __global__ __launch_bounds__(kRT) void wide_router(RouterArgs a) {
   const int nt = (int)min((int64_t)kRTok, a.M - t0);
   const int gl = tid % kGPP, tq = tid / kGPP;
   const bufview_t w2v = buf_view(a.w2, (uint32_t)(2 * ng * r) * 2);
+  // The group's decisions over the workgroup's tokens, one word per group, for
+  // the reorder (wide_reorder_bits).
+  __shared__ uint32_t s_word[kGPP];
+  auto words = [&](int last) {  // store and clear the words of the pass that ends with group `last`
+    __syncthreads();
+    if (tid <= last % kGPP) a.bits[(int64_t)(last - last % kGPP + tid) * a.bits_ld + blockIdx.x] = s_word[tid];
+    __syncthreads();
+    if (tid < kGPP) s_word[tid] = 0;
+  };
+  if (tid < kGPP) s_word[tid] = 0;
   for (int g0 = 0; g0 < ng; g0 += kGPP) {
     const int gc = min(kGPP, ng - g0);
+    if (a.bits && g0) words(g0 - 1);
     __syncthreads();  // s_h complete; the previous pass is done with s_w2
     {
       const int elems = 2 * gc * r;                 // bf16 values of this pass
@@ -136,33 +154,40 @@ __global__ __launch_bounds__(kRT) void wide_router(RouterArgs a) {
     __syncthreads();
     if (gl >= gc) continue;
     const int g = g0 + gl;
-    float w0[kRouterMaxRank], w1v[kRouterMaxRank];
+    float w0[RP], w1v[RP];
 #pragma unroll
-    for (int u = 0; u < kRouterMaxRank; ++u) {  // units past the rank weigh zero
+    for (int u = 0; u < RP; ++u) {  // units past the rank weigh zero
       w0[u] = u < r ? s_w2[2 * gl][u] : 0.f;
       w1v[u] = u < r ? s_w2[2 * gl + 1][u] : 0.f;
     }
+    uint32_t bits = 0;
     for (int t = tq; t < nt; t += kTPG) {
       float r0 = 0.f, r1 = 0.f;
 #pragma unroll
-      for (int u = 0; u < kRouterMaxRank; ++u) {  // terms past the rank add exact zeros
+      for (int u = 0; u < RP; ++u) {  // terms past the rank add exact zeros
         r0 = fmaf(s_h[t][u], w0[u], r0);
         r1 = fmaf(s_h[t][u], w1v[u], r1);
       }
       const int64_t row = t0 + t;
       a.mask[row * ng + g] = r0 >= r1 ? 1 : 0;
+      bits |= (uint32_t)(r0 >= r1) << t;
       if (a.logits) {
         a.logits[row * 2 * ng + 2 * g] = r0;
         a.logits[row * 2 * ng + 2 * g + 1] = r1;
       }
     }
+    if (a.bits && bits) atomicOr(&s_word[gl], bits);
   }
+  if (a.bits) words(ng - 1);
 }
 
 hipError_t launch_router(const RouterArgs& a, hipStream_t s) {
   if (a.M == 0) return hipSuccess;
   const int64_t blocks = (a.M + kRTok - 1) / kRTok;
-  WIDE_LAUNCH(wide_router, dim3((unsigned)blocks), dim3(kRT), 0, s, a);
+  if (a.r <= 16)
+    WIDE_LAUNCH_NAMED("wide_router", wide_router<16>, dim3((unsigned)blocks), dim3(kRT), 0, s, a);
+  else
+    WIDE_LAUNCH_NAMED("wide_router", wide_router<32>, dim3((unsigned)blocks), dim3(kRT), 0, s, a);
   return hipGetLastError();
 }
 
