@@ -685,7 +685,9 @@ constexpr int kd256_lds() {
 }
 static_assert(kd256_lds<0>() <= LDS_MAX && (int)sizeof(KdTables) <= RingKD<4>::LDS, "tables fit");
 
-template <int NWR, int BK, bool BUF>
+// SPLIT: the launch has tiles cut along k (the chunk's step offset costs the
+// uncut loop 0.9% where it is not needed).
+template <int NWR, int BK, bool BUF, bool SPLIT>
 __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
   static_assert(BK == t256::BK, "64-deep ring");
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
@@ -695,7 +697,7 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
   const uint16_t* zero = g_zero_blk;
   const int n_tiles = a.N / BN;
   int m_tile, n_tile, chunk = -1;
-  if ((int)blockIdx.x < a.tail_base) {
+  if (!SPLIT || (int)blockIdx.x < a.tail_base) {
     kd256_coords(n_tiles, a.tail_base, m_tile, n_tile);
   } else {  // a chunk of a tile of the last round
     const int rem = (int)((a.M + BM - 1) / BM) * n_tiles - a.tail_base, mt = rem / n_tiles;
@@ -712,7 +714,7 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
   const int spg = a.G / BK;  // k steps per group
   // the workgroup's k steps [u0, u1) and the groups [g0, g1) they touch
   int u0 = 0, u1 = a.K / BK;
-  if (chunk >= 0) {
+  if (SPLIT && chunk >= 0) {
     const int u = u1;
     u0 = u * chunk / a.split;
     u1 = u * (chunk + 1) / a.split;
@@ -733,9 +735,11 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
     if (t < a.M && wd * 32 < g1 && wd * 32 + 32 > g0)
       bits = mask_bits32(a.mask + t * ng + wd * 32, min(32, ng - wd * 32), ng);
     tb.mbits[r][wd] = bits;
-    const int lo = max(g0 - wd * 32, 0), hi = min(g1 - wd * 32, 32);
-    if (lo > 0) bits &= ~0u << min(lo, 31);
-    if (hi < 32) bits &= hi > 0 ? ~0u >> (32 - hi) : 0u;
+    if (SPLIT && chunk >= 0) {  // only the range's groups count
+      const int lo = max(g0 - wd * 32, 0), hi = min(g1 - wd * 32, 32);
+      if (lo > 0) bits &= ~0u << min(lo, 31);
+      if (hi < 32) bits &= hi > 0 ? ~0u >> (32 - hi) : 0u;
+    }
     if (bits) atomicOr(&tb.uni[wd], bits);
   }
   __syncthreads();
@@ -757,7 +761,7 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
   // group takes that group's part only.
   const int n_live = __builtin_amdgcn_readfirstlane(tb.n_live);
   int sbeg = 0, nsteps = n_live * spg;
-  if (n_live > 0) {
+  if (SPLIT && chunk >= 0 && n_live > 0) {
     const int gf = __builtin_amdgcn_readfirstlane((int)tb.groups[0]);
     const int gl = __builtin_amdgcn_readfirstlane((int)tb.groups[n_live - 1]);
     sbeg = max(0, u0 - gf * spg);
@@ -823,7 +827,7 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
   };
   const int lg = __builtin_ctz(a.G), lsp = lg - 6;  // G is a power of two, at least BK
   auto koff = [&](int s) {
-    s += sbeg;
+    if (SPLIT) s += sbeg;
     const int gi = s >> lsp;
     return group(gi) * a.G + (s & (spg - 1)) * BK;
   };
@@ -855,7 +859,7 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
   run_tile<Rg, 0>(smem, nsteps, koff, lda, ldb, bb, a.M - m0, acc);
 
   const int col = acc_col();
-  if (chunk >= 0) {  // fp32 partial sums, rows in tile order
+  if (SPLIT && chunk >= 0) {  // fp32 partial sums, rows in tile order
     const int64_t p0 = (int64_t)(a.tail_base / n_tiles) * BM, rows = a.M - p0;
     float* P = a.part + ((int64_t)chunk * rows + (m0 - p0)) * a.N + n0 + col;
 #pragma unroll
@@ -1123,18 +1127,22 @@ hipError_t launch_kd256(const KArgs& args, hipStream_t s) {
   if (a.K / a.G > kKd256MaxGroups) return hipErrorInvalidValue;
   const int ng = a.K / a.G;
   const bool buf = views_fit(a.M, a.K);
-  if (ng <= 32 && buf)
-    WIDE_RING_LAUNCH("wide_kd256<1>", (wide_kd256<1, 64, true>), kd256_lds<1>(), (unsigned)total, s, a);
-  else if (ng <= 32)
-    WIDE_RING_LAUNCH("wide_kd256<1>", (wide_kd256<1, 64, false>), kd256_lds<1>(), (unsigned)total, s, a);
-  else if (ng <= 128 && buf)
-    WIDE_RING_LAUNCH("wide_kd256<4>", (wide_kd256<4, 64, true>), kd256_lds<4>(), (unsigned)total, s, a);
-  else if (ng <= 128)
-    WIDE_RING_LAUNCH("wide_kd256<4>", (wide_kd256<4, 64, false>), kd256_lds<4>(), (unsigned)total, s, a);
-  else if (buf)
-    WIDE_RING_LAUNCH("wide_kd256<0>", (wide_kd256<0, 64, true>), kd256_lds<0>(), (unsigned)total, s, a);
-  else
-    WIDE_RING_LAUNCH("wide_kd256<0>", (wide_kd256<0, 64, false>), kd256_lds<0>(), (unsigned)total, s, a);
+#define WIDE_KD(NWR, BUF)                                                                                            \
+  do {                                                                                                               \
+    if (a.split > 1)                                                                                                 \
+      WIDE_RING_LAUNCH("wide_kd256<" #NWR ">", (wide_kd256<NWR, 64, BUF, true>), kd256_lds<NWR>(), (unsigned)total, s, \
+                       a);                                                                                           \
+    else                                                                                                             \
+      WIDE_RING_LAUNCH("wide_kd256<" #NWR ">", (wide_kd256<NWR, 64, BUF, false>), kd256_lds<NWR>(), (unsigned)total, s, \
+                       a);                                                                                           \
+  } while (0)
+  if (ng <= 32 && buf) WIDE_KD(1, true);
+  else if (ng <= 32) WIDE_KD(1, false);
+  else if (ng <= 128 && buf) WIDE_KD(4, true);
+  else if (ng <= 128) WIDE_KD(4, false);
+  else if (buf) WIDE_KD(0, true);
+  else WIDE_KD(0, false);
+#undef WIDE_KD
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.split < 2) return e;
   const int64_t p0 = (int64_t)(a.tail_base / (a.N / BN)) * BM, rows = a.M - p0;
