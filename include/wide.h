@@ -188,8 +188,9 @@ size_t wide_static_scratch_bytes(void);
  * G multiples of 16.
  * mask [M][n_q*hd/G]; idx/counts as for wide_ffn_masked (same routing
  * decision for both phases, Appendix B).
- * ws >= wide_workspace_size(phase == QKV ? WIDE_OP_QKV : WIDE_OP_O, dt, M,
- *       d_model, n_q*hd, G) bytes.
+ * ws of wide_workspace_size(phase == QKV ? WIDE_OP_QKV : WIDE_OP_O, dt, M,
+ *       d_model, n_q*hd, G) bytes (for O this includes up to 64 MiB of partial
+ *       sums, and less of it works as for wide_ffn_masked).
  */
 wide_status_t wide_qkvo_masked(wide_phase_t phase, wide_dtype_t dt, int64_t M,
                                int32_t d_model, int32_t n_q_heads,
