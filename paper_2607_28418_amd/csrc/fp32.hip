@@ -26,6 +26,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "launch.h"
+#include "tile256.h"
 
 namespace wide {
 
@@ -53,26 +54,28 @@ __device__ __forceinline__ void wave_run(int n, int& c0, int& c1) {
   c1 = (int)((int64_t)n * (w + 1) / NW);
 }
 
+// The lane's 16 bytes of row r of a tile whose rows start at `base`, K floats
+// apart: k from `k`, or zeros.
+__device__ __forceinline__ u32x4 row_ld(const float* base, int K, int r, int k, bool on) {
+  return on ? ldg16(base + (int64_t)r * K + k) : u32x4{0, 0, 0, 0};
+}
+
 // acc[v][i][j] += A fragment i x B fragment j of weight v over chunks
-// [c0, c1), D chunks in flight.  aoff(c, i): byte offset of the lane's 16
-// bytes of A fragment i at chunk c (called once per chunk, in order);
-// fragments past the views' ends read zeros.
-template <int NV, int F, int D, class AOff>
-__device__ __forceinline__ void k_loop(bufview_t av, const bufview_t (&wv)[NV], uint32_t row_bytes, int c0, int c1,
-                                       AOff aoff, f32x4 (&acc)[NV][F][F]) {
-  const int lane = lane_id();
-  const uint32_t woff = (uint32_t)(lane & 15) * row_bytes + (lane >> 4) * 16;
+// [c0, c1), D chunks in flight.  lda(c, i), ldw(v, c, j): the lane's 16 bytes
+// of A fragment i, and of B fragment j of weight v, at chunk c (lda is called
+// once per chunk, in order).
+template <int NV, int F, int D, class LdA, class LdW>
+__device__ __forceinline__ void k_loop(int c0, int c1, LdA lda, LdW ldw, f32x4 (&acc)[NV][F][F]) {
   struct Regs {
     u32x4 a[F], w[NV][F];
   };
   auto load = [&](int c, Regs& r) {
 #pragma unroll
-    for (int i = 0; i < F; ++i) r.a[i] = buf_ld16(av, aoff(c, i));
+    for (int i = 0; i < F; ++i) r.a[i] = lda(c, i);
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
-      for (int j = 0; j < F; ++j)
-        r.w[v][j] = buf_ld16s(wv[v], woff, (uint32_t)j * T * row_bytes + (uint32_t)c * (KC * 4));
+      for (int j = 0; j < F; ++j) r.w[v][j] = ldw(v, c, j);
   };
   auto mma = [&](const Regs& r) {
 #pragma unroll
@@ -128,7 +131,10 @@ __device__ __forceinline__ void reduce_tile(f32x4 (*red)[NW][kWave], const f32x4
 
 }  // namespace
 
-template <bool SWIGLU, int F>
+// BUF: 32 rows of either operand fit a buffer view (under 2^31 bytes) and a
+// lane keeps 32-bit byte offsets; rows of 2^24 floats or more take 64-bit
+// addresses.
+template <bool SWIGLU, int F, bool BUF>
 __global__ __launch_bounds__(NT) void wide_f32_nproj(F32NArgs a) {
   constexpr int NV = SWIGLU ? 2 : 1, TM = T * F;
   __shared__ f32x4 red[NV * F * F][NW][kWave];
@@ -155,10 +161,13 @@ __global__ __launch_bounds__(NT) void wide_f32_nproj(F32NArgs a) {
     return;
   }
   const uint32_t rb = (uint32_t)a.K * 4u;
-  const bufview_t av = buf_view(a.x + t0 * a.K, (uint32_t)rows * rb);
+  const float *xt = a.x + t0 * a.K, *wt[NV];
+  wt[0] = a.w0 + (int64_t)n0 * a.K;
+  if (SWIGLU) wt[NV - 1] = a.w1 + (int64_t)n0 * a.K;
+  const bufview_t av = buf_view(xt, BUF ? (uint32_t)rows * rb : 0u);
   bufview_t wv[NV];
-  wv[0] = buf_view(a.w0 + (int64_t)n0 * a.K, (uint32_t)cols * rb);
-  if (SWIGLU) wv[NV - 1] = buf_view(a.w1 + (int64_t)n0 * a.K, (uint32_t)cols * rb);
+  wv[0] = buf_view(wt[0], BUF ? (uint32_t)cols * rb : 0u);
+  if (SWIGLU) wv[NV - 1] = buf_view(wt[NV - 1], BUF ? (uint32_t)cols * rb : 0u);
   f32x4 acc[NV][F][F];
 #pragma unroll
   for (int v = 0; v < NV; ++v)
@@ -168,10 +177,19 @@ __global__ __launch_bounds__(NT) void wide_f32_nproj(F32NArgs a) {
       for (int j = 0; j < F; ++j) acc[v][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   int c0, c1;
   wave_run(a.K / KC, c0, c1);
-  const int lane = lane_id();
-  const uint32_t aoff = (uint32_t)(lane & 15) * rb + (lane >> 4) * 16;
-  k_loop<NV, F, 4>(av, wv, rb, c0, c1, [&](int c, int i) { return aoff + (uint32_t)i * T * rb + (uint32_t)c * (KC * 4); },
-                   acc);
+  const int l16 = lane_id() & 15, k4 = lane_id() / 16 * 4;
+  const uint32_t off = (uint32_t)l16 * rb + k4 * 4;  // within a fragment's chunk, both operands
+  k_loop<NV, F, 4>(
+      c0, c1,
+      [&](int c, int i) {
+        if constexpr (BUF) return buf_ld16(av, off + (uint32_t)i * T * rb + (uint32_t)c * (KC * 4));
+        else return row_ld(xt, a.K, i * T + l16, c * KC + k4, i * T + l16 < rows);
+      },
+      [&](int v, int c, int j) {
+        if constexpr (BUF) return buf_ld16s(wv[v], off, (uint32_t)j * T * rb + (uint32_t)c * (KC * 4));
+        else return row_ld(wt[v], a.K, j * T + l16, c * KC + k4, j * T + l16 < cols);
+      },
+      acc);
   reduce_tile<NV, F>(red, acc, [&](int r, int c, const float (&s)[NV]) {
     if (r >= rows || c >= cols) return;
     const bool on = !a.mask || s_on[r][c / T];
@@ -179,7 +197,7 @@ __global__ __launch_bounds__(NT) void wide_f32_nproj(F32NArgs a) {
   });
 }
 
-template <int F>
+template <int F, bool BUF>
 __global__ __launch_bounds__(NT) void wide_f32_kproj(F32KArgs a) {
   constexpr int TM = T * F, MAXG = 4096;
   __shared__ f32x4 red[F * F][NW][kWave];
@@ -206,8 +224,8 @@ __global__ __launch_bounds__(NT) void wide_f32_kproj(F32KArgs a) {
   }
   __syncthreads();
   const uint32_t rb = (uint32_t)a.K * 4u;
-  const bufview_t av = buf_view(a.a + t0 * a.K, (uint32_t)rows * rb);
-  const bufview_t wv[1] = {buf_view(a.w + (int64_t)n0 * a.K, (uint32_t)cols * rb)};
+  const float *at = a.a + t0 * a.K, *wt = a.w + (int64_t)n0 * a.K;
+  const bufview_t av = buf_view(at, BUF ? (uint32_t)rows * rb : 0u), wv = buf_view(wt, BUF ? (uint32_t)cols * rb : 0u);
   f32x4 acc[1][F][F];
 #pragma unroll
   for (int i = 0; i < F; ++i)
@@ -215,17 +233,26 @@ __global__ __launch_bounds__(NT) void wide_f32_kproj(F32KArgs a) {
     for (int j = 0; j < F; ++j) acc[0][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   int c0, c1;
   wave_run(a.K / KC, c0, c1);
-  const uint32_t aoff = (uint32_t)(lane & 15) * rb + (lane >> 4) * 16;
+  const int l16 = lane & 15, k4 = lane / 16 * 4;
+  const uint32_t off = (uint32_t)l16 * rb + k4 * 4;  // within a fragment's chunk, both operands
   // a chunk lies inside one group; the chunks are asked for in order
   int g = c0 * KC / a.G, left = (g + 1) * a.G - c0 * KC;
-  k_loop<1, F, 4>(av, wv, rb, c0, c1, [&](int c, int i) {
-    const bool on = (s_bits[i * T + (lane & 15)][g >> 6] >> (g & 63)) & 1u;
-    if (i == F - 1 && (left -= KC) == 0) {
-      ++g;
-      left = a.G;
-    }
-    return on ? aoff + (uint32_t)i * T * rb + (uint32_t)c * (KC * 4) : kOffNone;
-  }, acc);
+  k_loop<1, F, 4>(
+      c0, c1,
+      [&](int c, int i) {
+        const bool on = (s_bits[i * T + l16][g >> 6] >> (g & 63)) & 1u;
+        if (i == F - 1 && (left -= KC) == 0) {
+          ++g;
+          left = a.G;
+        }
+        if constexpr (BUF) return buf_ld16(av, on ? off + (uint32_t)i * T * rb + (uint32_t)c * (KC * 4) : kOffNone);
+        else return row_ld(at, a.K, i * T + l16, c * KC + k4, on);  // (rows past the tile's have no bit set)
+      },
+      [&](int, int c, int j) {
+        if constexpr (BUF) return buf_ld16s(wv, off, (uint32_t)j * T * rb + (uint32_t)c * (KC * 4));
+        else return row_ld(wt, a.K, j * T + l16, c * KC + k4, j * T + l16 < cols);
+      },
+      acc);
   reduce_tile<1, F>(red, acc, [&](int r, int c, const float (&s)[1]) {
     if (r < rows && c < cols) a.y[(t0 + r) * a.N + n0 + c] = s[0];
   });
@@ -239,33 +266,43 @@ namespace {
 // tokens, 512 outputs) down ran 12.8 and 11.0 us.
 int64_t tiles(int64_t M, int N, int tm) { return (M + tm - 1) / tm * ((N + tm - 1) / tm); }
 int frags(int64_t M, int N, bool pair) { return tiles(M, N, 2 * T) >= (pair ? 128 : 256) ? 2 : 1; }
+// Rows of which 32 do not fit a buffer view.
+bool long_rows(int K) { return (int64_t)2 * T * K * 4 > t256::kBufViewMax; }
 }  // namespace
 
 hipError_t launch_f32_nproj(const F32NArgs& a, bool swiglu, hipStream_t s) {
-  const int f = frags(a.M, a.N, swiglu);
+  const bool lr = long_rows(a.K);
+  const int f = lr ? 1 : frags(a.M, a.N, swiglu);
   const int64_t total = tiles(a.M, a.N, f * T);
   if (total == 0) return hipSuccess;
   const dim3 grid((unsigned)total), block(NT);
-  if (swiglu && f == 2)
-    WIDE_LAUNCH((wide_f32_nproj<true, 2>), grid, block, 0, s, a);
+  if (swiglu && lr)
+    WIDE_LAUNCH((wide_f32_nproj<true, 1, false>), grid, block, 0, s, a);
+  else if (swiglu && f == 2)
+    WIDE_LAUNCH((wide_f32_nproj<true, 2, true>), grid, block, 0, s, a);
   else if (swiglu)
-    WIDE_LAUNCH((wide_f32_nproj<true, 1>), grid, block, 0, s, a);
+    WIDE_LAUNCH((wide_f32_nproj<true, 1, true>), grid, block, 0, s, a);
+  else if (lr)
+    WIDE_LAUNCH((wide_f32_nproj<false, 1, false>), grid, block, 0, s, a);
   else if (f == 2)
-    WIDE_LAUNCH((wide_f32_nproj<false, 2>), grid, block, 0, s, a);
+    WIDE_LAUNCH((wide_f32_nproj<false, 2, true>), grid, block, 0, s, a);
   else
-    WIDE_LAUNCH((wide_f32_nproj<false, 1>), grid, block, 0, s, a);
+    WIDE_LAUNCH((wide_f32_nproj<false, 1, true>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_f32_kproj(const F32KArgs& a, hipStream_t s) {
-  const int f = frags(a.M, a.N, false);
+  const bool lr = long_rows(a.K);
+  const int f = lr ? 1 : frags(a.M, a.N, false);
   const int64_t total = tiles(a.M, a.N, f * T);
   if (total == 0) return hipSuccess;
   const dim3 grid((unsigned)total), block(NT);
-  if (f == 2)
-    WIDE_LAUNCH((wide_f32_kproj<2>), grid, block, 0, s, a);
+  if (lr)
+    WIDE_LAUNCH((wide_f32_kproj<1, false>), grid, block, 0, s, a);
+  else if (f == 2)
+    WIDE_LAUNCH((wide_f32_kproj<2, true>), grid, block, 0, s, a);
   else
-    WIDE_LAUNCH((wide_f32_kproj<1>), grid, block, 0, s, a);
+    WIDE_LAUNCH((wide_f32_kproj<1, true>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 

@@ -717,6 +717,31 @@ def test_fp32_tiles(orc, M, D, Dff, G):
     assert torch.equal(y, o)
 
 
+def test_fp32_rows_past_4gib():
+    """Sixteen rows of 2^26 floats are 4 GiB: more than a 32-bit byte offset
+    reaches.  Factors of -1, 0 and 1 keep every partial sum a whole number
+    below 2^24 (|sum| is about 5500), so the products are exact."""
+    say("fp32 rows of 2^26")
+    M, K = 16, 1 << 26
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x, w = (torch.randint(-1, 2, (M, K), generator=g, device=dev(), dtype=torch.int8).float() for _ in range(2))
+    step, heads = 1 << 22, 4096
+    ref = sum(x[:, i:i + step].double() @ w[:, i:i + step].double().T for i in range(0, K, step))
+    m = torch.ones((M, 1), dtype=torch.uint8, device=dev())
+    m[3] = 0
+    q, k, v = W.wide_qkvo_masked(W.PHASE_QKV, x, m, 16, 1, 1, 16, w_q=w, w_k=w, w_v=w)
+    assert torch.equal(q.double(), ref * m) and torch.equal(k.double(), ref) and torch.equal(v, k)
+    h = torch.empty((M, 16), device=dev())
+    W.wide_ffn_masked(x, w, w, w.view(K, 16), m, 16, h_out=h)
+    href = torch.nn.functional.silu(ref) * ref * m
+    assert (h.double() - href).abs().max() <= 1e-6 * href.abs().max()   # (a few fp32 ulps of the SiLU)
+    mo = (torch.rand((M, heads), generator=g, device=dev()) < 0.5).to(torch.uint8)
+    x *= mo.repeat_interleave(K // heads, dim=1)
+    ref = sum(x[:, i:i + step].double() @ w[:, i:i + step].double().T for i in range(0, K, step))
+    o = W.wide_qkvo_masked(W.PHASE_O, x, mo, K // heads, heads, 1, K // heads, w_o=w)
+    assert torch.equal(o.double(), ref)
+
+
 @pytest.mark.parametrize("M,D,ng,G,kind", [
     (200, 256, 128, 128, "ones"),      # 128 real tiles: cut to 64 columns
     (257, 256, 65, 128, "ones"),       # 130 real tiles: whole, in a launch sized for narrow ones
