@@ -1019,9 +1019,10 @@ hipError_t prepare() {
     WIDE_LAUNCH_NAMED(NAME "/bk64", (KERN), dim3(GRID), dim3(NT), LDSB, STREAM, ARGS);            \
   } while (0)
 
-// Buffer-view sources when the token-row operand fits a view (2 GB); the
-// same kernels on 64-bit addresses beyond.
-bool views_fit(int64_t rows, int K) { return rows * (int64_t)K * 2 <= kBufViewMax; }
+// Buffer-view sources when the token-row operand and a tile's weight panel
+// (at most BN rows) each fit a view (2 GB); the same kernels on 64-bit
+// addresses beyond.
+bool views_fit(int64_t rows, int K) { return std::max<int64_t>(rows, BN) * (int64_t)K * 2 <= kBufViewMax; }
 
 // Gate/up launches that wide_mn256_fit runs.  Sorted rows: 128-column tile
 // slots (real or not) such that at least a quarter of the tokens active per

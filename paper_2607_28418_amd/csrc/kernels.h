@@ -141,8 +141,8 @@ constexpr int kT256 = 256;
 // Gate/up: up to this many real 128-column tiles (half the CUs) run 64 columns wide.
 constexpr int kMN256NarrowTiles = 128;
 hipError_t launch_mn256(const MN256Args& a, bool swiglu, hipStream_t s);
-// The same on 64 (SwiGLU) or 128 output columns per tile; the x operand must
-// fit a buffer view (mn256_half_ok).
+// The same on 64 (SwiGLU) or 128 output columns per tile; both operands must
+// fit buffer views (mn256_half_ok).
 hipError_t launch_mn256_half(const MN256Args& a, bool swiglu, hipStream_t s);
 bool mn256_half_ok(int64_t M, int K);
 // The last, partial round of a dense-masked launch (see gemm256.hip): tiles

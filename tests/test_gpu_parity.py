@@ -742,6 +742,34 @@ def test_fp32_rows_past_4gib():
     assert torch.equal(o.double(), ref)
 
 
+def test_weight_panels_past_4gib():
+    """A tile's weight panel of 4 GiB (64 or 128 rows of very long tokens) does
+    not fit a buffer view even where the few tokens do.  Exact sums, as above;
+    the outputs are those sums rounded to bf16 once."""
+    say("weight panels of 4 GiB")
+    W.wide_set_option("decode_max_m", 0)
+    M, K = 2, 1 << 24
+    g = torch.Generator(device="cuda").manual_seed(9)
+
+    def sums(x, w):
+        n = x.shape[1] // 8
+        return sum(x[:, i * n:(i + 1) * n].float() @ w[:, i * n:(i + 1) * n].float().T for i in range(8)).double()
+
+    w = torch.randint(-1, 2, (128, K), generator=g, device=dev(), dtype=torch.int8).to(torch.bfloat16)
+    x = torch.randint(-1, 2, (M, 2 * K), generator=g, device=dev(), dtype=torch.int8).to(torch.bfloat16)
+    m = torch.ones((M, 1), dtype=torch.uint8, device=dev())
+    xq = x[:, :K].contiguous()
+    q, k, v = W.wide_qkvo_masked(W.PHASE_QKV, xq, m, 128, 1, 1, 128, w_q=w, w_k=w, w_v=w)
+    ref = sums(xq, w).to(torch.bfloat16)
+    assert torch.equal(q, ref) and torch.equal(k, ref) and torch.equal(v, ref)
+    w2 = w.view(64, 2 * K)
+    h = torch.empty((M, 64), dtype=torch.bfloat16, device=dev())
+    W.wide_ffn_masked(x, w2, w2, w.view(2 * K, 64), m, 64, h_out=h)
+    s = sums(x, w2)
+    href = torch.nn.functional.silu(s) * s
+    assert ((h.double() - href).abs() <= 2.0 ** -8 * href.abs() + 1e-30).all()
+
+
 @pytest.mark.parametrize("M,D,ng,G,kind", [
     (200, 256, 128, 128, "ones"),      # 128 real tiles: cut to 64 columns
     (257, 256, 65, 128, "ones"),       # 130 real tiles: whole, in a launch sized for narrow ones
