@@ -143,9 +143,18 @@ __global__ __launch_bounds__(kDT, HMAX <= 8 ? 2 : 1) void wide_attn_decode(AttnD
   if constexpr (BAL) {
     list_units(a, s_pre, s_sum);
     const int P = a.B * a.n_kv, q = __builtin_amdgcn_readfirstlane((int)s_sum[kDT / kWave]);
-    wave = blockIdx.x * 4 + w;
+    const int units = pre(P), nwg = (int)(((int64_t)units + 4 * q - 1) / (4 * q));
+    if ((int)blockIdx.x >= nwg) return;
+    // Workgroups with work take their waves' runs in order, neighbours on
+    // different XCDs.  In a head-major cache whose sequences all have the same
+    // length, a multiple of 1024 keys, that left an XCD always the same part of
+    // every pair (32 x 8192 keys, every other KV head off: 116 us), so long
+    // runs there go to each XCD in one piece (107; 113 in equal chunks, dealt
+    // the same way).  Other lengths, and 16 sequences of 4096 (8 units a wave),
+    // ran up to 4% slower that way, the token-major layout up to 8%.
+    const bool by_xcd = a.head_major && !a.kv_len && a.L % 1024 == 0 && q >= 16;
+    wave = (by_xcd ? t256::xcd_remap(blockIdx.x, nwg) : (int)blockIdx.x) * 4 + w;
     const int64_t u0 = (int64_t)wave * q;
-    const int units = pre(P);
     if (u0 >= units) return;
     u_end = (int)min(u0 + q, (int64_t)units);
     // the pair of unit u0, the last one with at most u0 units before it: 64

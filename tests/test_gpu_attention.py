@@ -350,6 +350,25 @@ def test_attention_decode_balanced_split(orc, B, L, n_q, n_kv, G, hm):
                    decode_bound(orc, *args, n_q, n_kv, hd), c.mask[b:b + 1], G, f"decode b={b} len={n}")
 
 
+def test_attention_decode_balanced_split_by_xcd(orc):
+    """Equal lengths of a head-major cache, 16 units a wave: the workgroups'
+    runs are dealt XCD by XCD, and each must still be taken once."""
+    say("attention decode balanced, by XCD")
+    B, L, n, hd = 64, 1024, 8, 128
+    c = synth.attn_decode_case(5, B, L, n, n, hd, n)
+    c.mask[:] = 1
+    q, k, v, m = (to_dev(a) for a in (c.q, head_major(c.k, n, hd), head_major(c.v, n, hd), c.mask))
+    o = torch.full_like(q, float("nan"))
+    W.wide_attention_decode(q, k, v, m, n, n, hd, hd, o=o, head_major=True)
+    torch.cuda.synchronize()
+    got = to_np64(o)
+    for b in range(0, B, 3):
+        args = (c.q[b:b + 1], c.k[b], c.v[b], c.mask[b:b + 1])
+        check_rows(got[b:b + 1], orc.attention(*args, 1, n, n, hd, False), decode_bound(orc, *args, n, n, hd),
+                   c.mask[b:b + 1], hd, f"decode b={b}")
+    assert np.isfinite(got).all()
+
+
 @pytest.mark.parametrize("kind", ["zeros", "ones"])
 def test_attention_decode_degenerate_masks(orc, kind):
     say("attention decode mask", kind)
