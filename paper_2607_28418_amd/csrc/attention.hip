@@ -95,38 +95,46 @@ __global__ __launch_bounds__(kAT, 2) void wide_attn_fwd(AttnArgs a) {
   const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
   const int64_t ldq = (int64_t)a.n_q * kHd;
   const int64_t M = a.M;
-  int hbk, b, slot;
-  auto classic = [&](int lid) {
+  int hbk = 0, b = 0, slot = 0;
+  int s0 = 0, s1 = 0;  // active run of (sequence b, the head block's group)
+  if ((int)blockIdx.x < n_classic) {
+    const int lid = t256::xcd_remap(blockIdx.x, n_classic);
     hbk = lid / per_hb;
-    const int rem = lid - hbk * per_hb;
+    const int rem = lid - hbk * per_hb, gg = hbk * HB / a.hpg, cnt = a.cnt[gg];
     // Long key ranges first, over all sequences: a sequence's tiles past its
     // active rows then come first and exit, and the real ones follow in one
     // run that the dispatcher spreads over the CUs.  (Sequence by sequence,
     // four of 500 tokens at keep 0.5 put two tiles each on half of the CUs and
-    // none on the others: 62 us, now 52.)
-    slot = a.n_slots - 1 - rem / a.n_seq;
-    b = rem % a.n_seq;
-  };
-  auto rows_of = [&](int hk, int bb, int& s0, int& s1) {  // active run of (sequence bb, group of hk)
-    const int gg = hk * HB / a.hpg;
-    s0 = 0;
-    s1 = a.cnt[gg];
+    // none on the others: 62 us, now 52.)  Where more than 5/8 of the rows are
+    // active there is little to skip, and walking many short sequences in turn
+    // costs more than it gains (32 of 256 tokens, all active: 72 us sequence
+    // by sequence, 88 over all of them), so there they go in blocks of
+    // seq_block (68 us).  Both places' runs are loaded beside the count.
+    const int up = rem / a.n_seq;
+    slot = a.n_slots - 1 - up;
+    b = rem - up * a.n_seq;
+    s1 = cnt;
     if (a.seq_off) {
-      s0 = a.seq_off[gg * (a.n_seq + 1) + bb];
-      s1 = a.seq_off[gg * (a.n_seq + 1) + bb + 1];
+      const int32_t* so = a.seq_off + gg * (a.n_seq + 1);
+      s0 = so[b];
+      s1 = so[b + 1];
+      if (a.seq_block < a.n_seq) {
+        const int per_block = a.seq_block * a.n_slots, blk = rem / per_block, r = rem - blk * per_block;
+        const int bb0 = blk * a.seq_block, nb = min(a.seq_block, a.n_seq - bb0), u = r / nb, bb = bb0 + r - u * nb;
+        const int t0 = so[bb], t1 = so[bb + 1];
+        if (8 * (int64_t)cnt > 5 * M) {
+          slot = a.n_slots - 1 - u;
+          b = bb;
+          s0 = t0;
+          s1 = t1;
+        }
+      }
     }
-  };
-
-  // Inactive rows of a sequence sit at idx_g[cnt_g + (b*T_q - s0) ...]; slot
-  // i of the classic mapping clears rows [i*BMW, (i+1)*BMW) of that run for
-  // its HB heads.
-  if ((int)blockIdx.x < n_classic) {
-    classic(t256::xcd_remap(blockIdx.x, n_classic));
+    // Inactive rows of a sequence sit at idx_g[cnt_g + (b*T_q - s0) ...]; slot
+    // i of the classic mapping clears rows [i*BMW, (i+1)*BMW) of that run for
+    // its HB heads.
     constexpr int CPR = HB * kHd / 8;  // 16-byte chunks per row
-    int s0, s1;
-    rows_of(hbk, b, s0, s1);
-    const int gg = hbk * HB / a.hpg;
-    const int64_t ib = (int64_t)a.cnt[gg] + ((int64_t)b * a.T_q - s0);
+    const int64_t ib = (int64_t)cnt + ((int64_t)b * a.T_q - s0);
     const int r0 = slot * BMW, r1 = min(a.T_q - (s1 - s0), r0 + BMW);
     const int32_t* ig = a.idx + (int64_t)gg * M;
     for (int i = tid; i < (r1 - r0) * CPR; i += kAT) {
@@ -146,19 +154,17 @@ __global__ __launch_bounds__(kAT, 2) void wide_attn_fwd(AttnArgs a) {
     const int32_t* tab = a.sched + kAttnSchedHead + kAttnMaxUnits;
     hbk = tab[rank] >> 16;
     slot = tab[rank] & 0xffff;
-    b = 0;
+    b = s0 = 0;
+    s1 = a.cnt[hbk * HB / a.hpg];
     n_chunk = tab[a.split_tiles + rank];
     part_unit = tab[2 * a.split_tiles + rank] + chunk;
     chunk_tiles = a.sched[2];
-  } else {
-    if ((int)blockIdx.x >= n_classic) return;
-    classic(t256::xcd_remap(blockIdx.x, n_classic));
+  } else if ((int)blockIdx.x >= n_classic) {
+    return;
   }
   const int h0 = hbk * HB;
   const int g = h0 / a.hpg, hkv = h0 / a.qpk;
   const int32_t* idx_g = a.idx + (int64_t)g * M;
-  int s0, s1;
-  rows_of(hbk, b, s0, s1);
   const int c = s1 - s0;  // active rows of (sequence b, group g)
   const int64_t seq0 = (int64_t)b * a.T_q;
   const int m0 = slot * BMW;
@@ -753,6 +759,7 @@ hipError_t launch_attention(AttnArgs a, const uint16_t* v, int32_t* seq_off, hip
     a.split_tiles = 0;
   }
   a.split_rounds = g_attn_split_rounds;
+  a.seq_block = hb == 4 && a.T_q < 1024 ? 4 : 8;
   const int n_vt = a.n_seq * a.n_kv * (a.T_kp / 64);
   const int n_off = a.n_seq > 1 ? (a.ng * (a.n_seq + 1) + 3) / 4 : 0;
   WIDE_LAUNCH(wide_attn_prep, dim3((unsigned)(n_vt + n_off + (a.sched ? 1 : 0))), dim3(kAT), 0, s, a, v, seq_off,

@@ -64,6 +64,17 @@ def test_attention_matches_oracle(orc, n_seq, T_q, T_k, n_q, n_kv, G, causal, ma
     run_case(orc, n_seq, T_q, T_k, n_q, n_kv, G, causal, mask=mask, qk_std=qk_std, seed=T_q + n_q)
 
 
+@pytest.mark.parametrize("n_seq,T_q,T_k,n_q,n_kv,G,keep", [
+    (11, 100, 100, 8, 2, 512, 1.0),    # blocks of four sequences, the last of three
+    (9, 70, 130, 4, 4, 128, 0.9),      # blocks of eight, the last of one
+    (11, 100, 100, 8, 2, 512, 0.5),    # mostly inactive: all sequences at once
+])
+def test_attention_sequences_in_blocks(orc, n_seq, T_q, T_k, n_q, n_kv, G, keep):
+    """Groups with most rows active deal their tiles in blocks of sequences."""
+    say("attention blocks", n_seq, T_q, T_k, n_q, n_kv, G, keep)
+    run_case(orc, n_seq, T_q, T_k, n_q, n_kv, G, True, mask="bernoulli", keep=keep, seed=n_seq + T_q)
+
+
 @pytest.mark.parametrize("n_seq,T_q,T_k,n_q,n_kv,G,causal,leftpad", [
     (3, 200, 200, 8, 2, 512, True, [0, 37, 130]),       # padding queries see no key: +0
     (2, 70, 130, 8, 2, 256, True, [60, 129]),           # after a prefix; the tile of key 129 only
