@@ -1025,7 +1025,7 @@ wide_status_t wide_qkvo_masked(wide_phase_t phase, wide_dtype_t dt, int64_t M, i
         ma.reg[iq] = wide::MN256Region{wq, nullptr, static_cast<uint16_t*>(q), d.Nq, d.G, wide::kMN256Sorted,
                                        ng * ma.m_tiles * (d.G / T)};
       }
-      ma.tail = g_mn_tail && wide::mn256_tail_ok(ma, 256) ? 1 : 0;
+      ma.tail = g_mn_tail && wide::mn256_tail_ok(ma) ? 1 : 0;
       ma.tail_ws = tail_ws;
       if ((e = wide::launch_mn256(ma, false, stream)) != hipSuccess) return hip_fail(e, "mn256 qkv");
       return ok();

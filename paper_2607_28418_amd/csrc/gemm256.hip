@@ -556,8 +556,8 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256_fit(MN256Args a) {
   }
 }
 
-// Finish the XCDs' tail tiles: add each tile's chunks in order, then the
-// mn256 epilogue (SwiGLU or plain, rows back to token order).  Workgroup
+// Finish the XCDs' tail tiles (Q/K/V): add each tile's chunks in order, then the
+// mn256 epilogue (rows back to token order).  Workgroup
 // (xcd, k, rb) takes kTailRows rows of tail tile k; each thread
 // loads the chunks of its elements together (independent 16-byte loads) and adds
 // them in chunk order.  Bound by the partial tiles' bytes per CU, so rows past
@@ -566,22 +566,20 @@ __global__ __launch_bounds__(NT, 1) void wide_mn256_fit(MN256Args a) {
 // 14).
 constexpr int kTailRows = 8;
 constexpr int kTailTiles = kMN256TailJobs / 2;  // at most: two chunks each
-template <bool SWIGLU>
 __global__ __launch_bounds__(NT) void wide_mn256_tail(MN256Args a) {
-  constexpr int BNO = SWIGLU ? 128 : 256;
-  constexpr int PER = kTailRows * BNO / NT / 4;  // runs of four columns per thread
+  constexpr int PER = kTailRows * BN / NT / 4;  // runs of four columns per thread
   __shared__ int map[kTailRows];
   static_assert(kTailRows <= NT, "one thread per row for the row map");
   const int rb = blockIdx.x % (BM / kTailRows);
   const int k = (blockIdx.x / (BM / kTailRows)) % kTailTiles;
   const int xcd = blockIdx.x / (BM / kTailRows * kTailTiles);
-  const MN256Tail t = mn256_tail<BNO>(a, xcd);
+  const MN256Tail t = mn256_tail<BN>(a, xcd);
   if (k >= t.n) return;
   int ri, local, g, m_tile, nt_in;
   mn256_tail_tile(t, k, ri, local);
   const MN256Region R = ri == 0 ? a.reg[0] : ri == 1 ? a.reg[1] : a.reg[2];
-  mn256_coords<BNO>(a, R, xcd, local, g, m_tile, nt_in);
-  const int n0 = g * R.gw + nt_in * BNO;
+  mn256_coords<BN>(a, R, xcd, local, g, m_tile, nt_in);
+  const int n0 = g * R.gw + nt_in * BN;
   const int32_t* rows = R.masked == kMN256Sorted ? a.idx + (int64_t)g * a.M : nullptr;
   const int64_t cnt = R.masked == kMN256Sorted ? (int64_t)a.cnt[g] : a.M;
   const int64_t p0 = (int64_t)m_tile * BM + rb * kTailRows;
@@ -592,32 +590,25 @@ __global__ __launch_bounds__(NT) void wide_mn256_tail(MN256Args a) {
 #pragma unroll
   for (int e = 0; e < PER; ++e) {  // four columns at a time
     const int i = (e * NT + tid) * 4;
-    const int r = i / BNO, c = i % BNO;
+    const int r = i / BN, c = i % BN;
     const int tok = map[r];
     if (tok < 0) continue;
     const bool live = p0 + r < cnt;  // past the active rows: +0, nothing was written
     const float* Pe = P + (rb * kTailRows + r) * BN + c;
-    f32x4 v0[kMN256TailMaxSplit], v1[kMN256TailMaxSplit];
+    f32x4 v[kMN256TailMaxSplit];
 #pragma unroll
     for (int q = 0; q < kMN256TailMaxSplit; ++q) {
       const bool on = live && q < t.split;
-      const float* Pq = Pe + (int64_t)(on ? q : 0) * (BM * BN);
-      v0[q] = on ? *reinterpret_cast<const f32x4*>(Pq) : f32x4{0.f, 0.f, 0.f, 0.f};
-      v1[q] = SWIGLU && on ? *reinterpret_cast<const f32x4*>(Pq + 128) : f32x4{0.f, 0.f, 0.f, 0.f};
+      v[q] = on ? *reinterpret_cast<const f32x4*>(Pe + (int64_t)q * (BM * BN)) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    f32x4 s0{0.f, 0.f, 0.f, 0.f}, s1{0.f, 0.f, 0.f, 0.f};
+    f32x4 s{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int q = 0; q < kMN256TailMaxSplit; ++q) {  // chunk order
-      s0 += v0[q];
-      s1 += v1[q];
-    }
+    for (int q = 0; q < kMN256TailMaxSplit; ++q) s += v[q];  // chunk order
     // (token-order groups are at least 16 columns wide, so the four share one)
     const bool on = live && (R.masked != kMN256TokenOrder || a.mask[(int64_t)tok * a.mask_ng + (n0 + c) / a.mask_G] != 0);
-    float o[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) o[j] = on ? (SWIGLU ? silu(s0[j]) * s1[j] : s0[j]) : 0.f;
+    if (!on) s = f32x4{0.f, 0.f, 0.f, 0.f};
     *reinterpret_cast<uint2*>(R.out + (int64_t)tok * R.ldo + n0 + c) =
-        uint2{pack_bf16x2_hw(o[0], o[1]), pack_bf16x2_hw(o[2], o[3])};
+        uint2{pack_bf16x2_hw(s[0], s[1]), pack_bf16x2_hw(s[2], s[3])};
   }
 }
 
@@ -1029,7 +1020,7 @@ bool views_fit(int64_t rows, int K) { return std::max<int64_t>(rows, BN) * (int6
 // group could fit kMN256NarrowTiles.  Token order: every tile is real.
 static bool mn256_fit(const MN256Args& a) {
   const MN256Region& R = a.reg[0];
-  return a.n_regions == 1 && !a.tail && views_fit(a.M, a.K) &&
+  return a.n_regions == 1 && views_fit(a.M, a.K) &&
          (R.masked == kMN256Sorted ? R.tiles <= 4 * kMN256NarrowTiles && R.gw % 128 == 0 && R.ldo % R.gw == 0
                                    : R.masked == kMN256TokenOrder && R.tiles <= kMN256NarrowTiles);
 }
@@ -1051,6 +1042,7 @@ hipError_t launch_mn256(const MN256Args& a, bool swiglu, hipStream_t s) {
   int64_t total = 0;
   for (int i = 0; i < a.n_regions; ++i) total += a.reg[i].tiles;
   if (total == 0) return hipSuccess;
+  if (swiglu && a.tail) return hipErrorInvalidValue;  // Q/K/V only
   total = 8 * (int64_t)(swiglu ? mn256_shares<128>(a) : mn256_shares<256>(a));
   if (swiglu && mn256_fit(a)) {
     MN256Region r = a.reg[0];
@@ -1071,20 +1063,16 @@ hipError_t launch_mn256(const MN256Args& a, bool swiglu, hipStream_t s) {
     WIDE_RING_LAUNCH("wide_mn256<false>", (wide_mn256<false, 64, false>), RingMN::LDS, (unsigned)total, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !a.tail) return e;
-  const dim3 tg(8 * kTailTiles * (BM / kTailRows));
-  if (swiglu)
-    WIDE_LAUNCH(wide_mn256_tail<true>, tg, dim3(NT), 0, s, a);
-  else
-    WIDE_LAUNCH(wide_mn256_tail<false>, tg, dim3(NT), 0, s, a);
+  WIDE_LAUNCH(wide_mn256_tail, dim3(8 * kTailTiles * (BM / kTailRows)), dim3(NT), 0, s, a);
   return hipGetLastError();
 }
 
-bool mn256_tail_ok(const MN256Args& a, int bno) {
+bool mn256_tail_ok(const MN256Args& a) {
   for (int i = 0; i < a.n_regions; ++i) {
     const MN256Region& R = a.reg[i];
     if (R.masked != kMN256Sorted) continue;  // dense and token-order regions: every tile is real
-    const int share = mn256_share(R.tiles), per_group = R.gw / bno * a.m_tiles;
-    if (!(a.order && !a.mblock && R.gw / bno <= 4 && 8 * share == R.tiles && share % per_group == 0))
+    const int share = mn256_share(R.tiles), per_group = R.gw / BN * a.m_tiles;
+    if (!(a.order && !a.mblock && R.gw / BN <= 4 && 8 * share == R.tiles && share % per_group == 0))
       return false;
   }
   return true;

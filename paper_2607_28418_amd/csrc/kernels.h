@@ -133,9 +133,9 @@ struct MN256Args {
 constexpr int kMN256TailJobs = 32;  // tail workgroups per XCD (its CUs)
 constexpr int kMN256TailMaxSplit = 8;  // chunks per tail tile at most
 constexpr size_t kMN256TailFloats = (size_t)8 * kMN256TailJobs * 256 * 256;
-// Host view of the launch condition: every region dense, or masked with the
-// ordered tile order (bno: output columns per tile, 128 with SwiGLU else 256).
-bool mn256_tail_ok(const MN256Args& a, int bno);
+// Host view of the launch condition (plain projections only): every region
+// dense, or masked with the ordered tile order.
+bool mn256_tail_ok(const MN256Args& a);
 
 constexpr int kT256 = 256;
 // Gate/up: up to this many real 128-column tiles (half the CUs) run 64 columns wide.
