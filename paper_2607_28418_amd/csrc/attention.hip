@@ -98,7 +98,7 @@ __global__ __launch_bounds__(kAT, 2) void wide_attn_fwd(AttnArgs a) {
   int hbk = 0, b = 0, slot = 0;
   int s0 = 0, s1 = 0;  // active run of (sequence b, the head block's group)
   if ((int)blockIdx.x < n_classic) {
-    const int lid = t256::xcd_remap(blockIdx.x, n_classic);
+    const int lid = xcd_remap(blockIdx.x, n_classic);
     hbk = lid / per_hb;
     const int rem = lid - hbk * per_hb, gg = hbk * HB / a.hpg, cnt = a.cnt[gg];
     // Long key ranges first, over all sequences: a sequence's tiles past its
@@ -109,21 +109,19 @@ __global__ __launch_bounds__(kAT, 2) void wide_attn_fwd(AttnArgs a) {
     // active there is little to skip, and walking many short sequences in turn
     // costs more than it gains (32 of 256 tokens, all active: 72 us sequence
     // by sequence, 88 over all of them), so there they go in blocks of
-    // seq_block (68 us).  Both places' runs are loaded beside the count.
-    const int up = rem / a.n_seq;
-    slot = a.n_slots - 1 - up;
-    b = rem - up * a.n_seq;
+    // seq_block (66 us).  Both places' runs are loaded beside the count.
+    attn_place(rem, a.n_seq, a.n_slots, a.n_seq, slot, b);
     s1 = cnt;
     if (a.seq_off) {
       const int32_t* so = a.seq_off + gg * (a.n_seq + 1);
       s0 = so[b];
       s1 = so[b + 1];
       if (a.seq_block < a.n_seq) {
-        const int per_block = a.seq_block * a.n_slots, blk = rem / per_block, r = rem - blk * per_block;
-        const int bb0 = blk * a.seq_block, nb = min(a.seq_block, a.n_seq - bb0), u = r / nb, bb = bb0 + r - u * nb;
+        int slot_b, bb;
+        attn_place(rem, a.n_seq, a.n_slots, a.seq_block, slot_b, bb);
         const int t0 = so[bb], t1 = so[bb + 1];
         if (8 * (int64_t)cnt > 5 * M) {
-          slot = a.n_slots - 1 - u;
+          slot = slot_b;
           b = bb;
           s0 = t0;
           s1 = t1;

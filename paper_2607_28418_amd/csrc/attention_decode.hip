@@ -153,7 +153,7 @@ __global__ __launch_bounds__(kDT, HMAX <= 8 ? 2 : 1) void wide_attn_decode(AttnD
     // the same way).  Other lengths, and 16 sequences of 4096 (8 units a wave),
     // ran up to 4% slower that way, the token-major layout up to 8%.
     const bool by_xcd = a.head_major && !a.kv_len && a.L % 1024 == 0 && q >= 16;
-    wave = (by_xcd ? t256::xcd_remap(blockIdx.x, nwg) : (int)blockIdx.x) * 4 + w;
+    wave = (by_xcd ? xcd_remap(blockIdx.x, nwg) : (int)blockIdx.x) * 4 + w;
     const int64_t u0 = (int64_t)wave * q;
     if (u0 >= units) return;
     u_end = (int)min(u0 + q, (int64_t)units);
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kDT, HMAX <= 8 ? 2 : 1) void wide_attn_decode(AttnD
     // XCD (workgroups are dealt round-robin to the 8 XCDs) takes a contiguous
     // range of them, i.e. whole sequences, so masks that switch whole KV heads
     // off still leave every XCD the same share of the work.
-    const int64_t item = (int64_t)t256::xcd_remap(blockIdx.x, gridDim.x) * 4 + w;
+    const int64_t item = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * 4 + w;
     if (item >= (int64_t)a.B * a.n_kv * a.n_chunks) return;
     p = (int)(item / a.n_chunks);
     j_begin = (int)(item % a.n_chunks) * a.chunk;

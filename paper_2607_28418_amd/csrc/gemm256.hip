@@ -153,7 +153,7 @@ __host__ __device__ __forceinline__ bool mn256_mblocked(const MN256Args& a, cons
 // Workgroups per XCD of a region.
 template <int BNO>
 __host__ __device__ __forceinline__ int mn256_region_share(const MN256Args& a, const MN256Region& R) {
-  if (mn256_mblocked<BNO>(a, R)) return (R.tiles / a.m_tiles + 7) / 8 * a.m_tiles;
+  if (mn256_mblocked<BNO>(a, R)) return mblock_share(R.tiles / a.m_tiles, a.m_tiles);
   return mn256_share(R.tiles);
 }
 
@@ -165,22 +165,8 @@ __device__ __forceinline__ void mn256_coords(const MN256Args& a, const MN256Regi
   const int ntpg = R.gw / BNO;  // tiles per group
   const int per_group = ntpg * a.m_tiles;
   if (mn256_mblocked<BNO>(a, R)) {
-    // the XCD's column tiles [c0, c0 + n) in two halves, each walked m-tile by
-    // m-tile (m_tile = a.m_tiles: padding)
-    const int cols = R.tiles / a.m_tiles;
-    int c0 = cols * xcd / 8, n = cols * (xcd + 1) / 8 - c0, l = local;
-    if (BNO != 64 && n >= 4 * ntpg) {
-      const int h = n / 2;
-      if (l < h * a.m_tiles) {
-        n = h;
-      } else {
-        l -= h * a.m_tiles;
-        c0 += h;
-        n -= h;
-      }
-    }
-    m_tile = n ? min(l / n, a.m_tiles) : a.m_tiles;
-    const int col = c0 + (n ? l % n : 0);
+    int col;
+    mblock_place(R.tiles / a.m_tiles, a.m_tiles, ntpg, BNO != 64, xcd, local, col, m_tile);
     g = col / ntpg;
     nt_in = col % ntpg;
     return;
@@ -642,24 +628,6 @@ __global__ __launch_bounds__(NT) void wide_mn256_tail(MN256Args a) {
 // activations too.  Llama-3-8B down, kernel plus finish: 300 tokens 253 ->
 // 55 + 9 us, 1000 tokens 274 -> 105 + 14, 2048 tokens 284 -> 190 + 15; at
 // 3000 tokens (192 of 256 tiles) a split would not fill the chip better.
-__device__ __forceinline__ void kd256_coords(int n_tiles, int total, int& m_tile, int& n_tile) {
-  const bool blocks = n_tiles % 2 == 0 && n_tiles <= 256 && 256 % n_tiles == 0 && (256 / n_tiles) % 4 == 0;
-  const int rounds = blocks ? total / 256 : 0;
-  const int id = blockIdx.x;
-  if (id < rounds * 256) {
-    const int xcd = id % 8, local = id / 8;  // workgroups are dealt round-robin to the 8 XCDs
-    const int r = local / 32, q = local % 32;
-    const int mr = 256 / n_tiles, bm = mr / 4, bn = n_tiles / 2;
-    m_tile = r * mr + (xcd % 4) * bm + q % bm;
-    n_tile = (xcd / 4) * bn + q / bm;
-    return;
-  }
-  const int base = rounds * 256;
-  const int tile = base + xcd_remap(id - base, total - base);  // m-major: n-tiles share the A panel
-  m_tile = tile / n_tiles;
-  n_tile = tile % n_tiles;
-}
-
 // Mask tables of a dense-masked tile: the rows' mask bits, the groups some
 // row uses (ascending), their union and count.  With NWR > 0 they live in the
 // ring's LDS before its first load and move to registers (the ring then takes
@@ -689,13 +657,10 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
   const int n_tiles = a.N / BN;
   int m_tile, n_tile, chunk = -1;
   if (!SPLIT || (int)blockIdx.x < a.tail_base) {
-    kd256_coords(n_tiles, a.tail_base, m_tile, n_tile);
+    kd256_coords(blockIdx.x, n_tiles, a.tail_base, m_tile, n_tile);
   } else {  // a chunk of a tile of the last round
-    const int rem = (int)((a.M + BM - 1) / BM) * n_tiles - a.tail_base, mt = rem / n_tiles;
-    const int j = xcd_remap(blockIdx.x - a.tail_base, rem * a.split);
-    chunk = j / rem;
-    m_tile = a.tail_base / n_tiles + j % rem % mt;
-    n_tile = j % rem / mt;
+    kd256_chunk(blockIdx.x - a.tail_base, (int)((a.M + BM - 1) / BM), n_tiles, a.tail_base, a.split, chunk, m_tile,
+                n_tile);
   }
   const int64_t m0 = (int64_t)m_tile * BM;
   const int n0 = n_tile * BN;
@@ -705,11 +670,7 @@ __global__ __launch_bounds__(NT, 1) void wide_kd256(KArgs a) {
   const int spg = a.G / BK;  // k steps per group
   // the workgroup's k steps [u0, u1) and the groups [g0, g1) they touch
   int u0 = 0, u1 = a.K / BK;
-  if (SPLIT && chunk >= 0) {
-    const int u = u1;
-    u0 = u * chunk / a.split;
-    u1 = u * (chunk + 1) / a.split;
-  }
+  if (SPLIT && chunk >= 0) kd256_steps(a.K, chunk, a.split, u0, u1);
   const int g0 = u0 / spg, g1 = (u1 + spg - 1) / spg;
 
   if (tid < nw) tb.uni[tid] = 0u;
@@ -1078,26 +1039,7 @@ bool mn256_tail_ok(const MN256Args& a) {
   return true;
 }
 
-// Chunks of the last round: as many as fill the 256 CUs once, each at least
-// kKdMinSteps deep.
-constexpr int kKdMaxSplit = 16, kKdMinSteps = 4;
-Kd256Tail kd256_tail(int64_t M, int N, int K, int ng, size_t avail) {
-  const int n_tiles = N / BN;
-  const int64_t m_tiles = (M + BM - 1) / BM, total = m_tiles * n_tiles;
-  Kd256Tail t{(int)total, 1, M};
-  if (total == 0 || n_tiles > 256) return t;
-  const int mr = 256 / n_tiles;  // m-tiles of a full round
-  const int64_t mb = m_tiles / mr * mr, rem = total - mb * n_tiles, rows = M - mb * BM;
-  // (rows the mask-pattern order may move between a whole and a split tile
-  // keep one summation order: there only launches of less than a round split)
-  if (rem == 0 || (mb > 0 && ng > 1 && ng <= kPatternMaxGroups)) return t;
-  int64_t split = 256 / rem;
-  if (split > kKdMaxSplit) split = kKdMaxSplit;
-  if (split > K / BK / kKdMinSteps) split = K / BK / kKdMinSteps;
-  if (split > (int64_t)(avail / ((size_t)rows * N))) split = (int64_t)(avail / ((size_t)rows * N));
-  if (split >= 2) t = Kd256Tail{(int)(mb * n_tiles), (int)split, mb * BM};
-  return t;
-}
+static_assert(kKdTile == BM && kKdTile == BN && kKdStep == BK, "tile_order.h");
 size_t kd256_part_floats(int64_t M, int N, int K, int ng) {
   const Kd256Tail t = kd256_tail(M, N, K, ng, SIZE_MAX);
   return t.split > 1 ? (size_t)t.split * (size_t)(M - t.m0) * (size_t)N : 0;

@@ -7,6 +7,8 @@
 
 #include <atomic>
 
+#include "tile_order.h"
+
 namespace wide {
 
 // ---- mask reorder ---------------------------------------------------------
@@ -19,9 +21,8 @@ size_t reorder_scratch_ints(int64_t M, int n_groups);
 constexpr int kReorderBitsMax = 32768;
 hipError_t launch_reorder_bits(const uint32_t* bits, int M, int n_groups, int32_t* idx, int32_t* counts,
                                hipStream_t s);
-// Token order by mask pattern (n_groups <= 8): perm[M] lists the tokens
+// Token order by mask pattern (n_groups <= kPatternMaxGroups): perm[M] lists the tokens
 // grouped by their mask row.  scratch: pattern_scratch_ints(M) ints.
-constexpr int kPatternMaxGroups = 8;
 size_t pattern_scratch_ints(int64_t M);
 hipError_t launch_pattern_order(const uint8_t* mask, int64_t M, int n_groups, int32_t* perm, int32_t* scratch,
                                 hipStream_t s);
@@ -145,16 +146,8 @@ hipError_t launch_mn256(const MN256Args& a, bool swiglu, hipStream_t s);
 // fit buffer views (mn256_half_ok).
 hipError_t launch_mn256_half(const MN256Args& a, bool swiglu, hipStream_t s);
 bool mn256_half_ok(int64_t M, int K);
-// The last, partial round of a dense-masked launch (see gemm256.hip): tiles
-// [base, total) are each run by `split` workgroups (1: not split), token rows
-// from m0 on; at most `avail` floats of partial sums.
-struct Kd256Tail {
-  int base, split;
-  int64_t m0;
-};
-Kd256Tail kd256_tail(int64_t M, int N, int K, int ng, size_t avail);
+// Floats of partial sums that kd256_tail can use.
 size_t kd256_part_floats(int64_t M, int N, int K, int ng);
-constexpr size_t kKd256PartMaxFloats = (size_t)256 * 256 * 256;  // at most 256 chunks of one tile's sums
 hipError_t launch_kd256(const KArgs& a, hipStream_t s);
 hipError_t launch_ks256(const KArgs& a, hipStream_t s);
 constexpr int kKd256MaxGroups = 512;

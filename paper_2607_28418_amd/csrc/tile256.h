@@ -37,6 +37,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "tile_order.h"
 
 namespace wide {
 namespace t256 {
@@ -365,14 +366,6 @@ __device__ __forceinline__ int acc_row(int fm, int i) {
   return (wave_id() >> 1) * 128 + fm * 32 + (i >> 2) * 8 + (lane_id() >> 5) * 4 + (i & 3);
 }
 __device__ __forceinline__ int acc_col() { return lane_id() & 31; }
-
-// Workgroup id -> tile id: each XCD (workgroups are dealt round-robin to the
-// 8 XCDs) walks a contiguous range of tile ids.
-__device__ __forceinline__ int xcd_remap(int id, int n) {
-  const int q = n / 8, r = n % 8;
-  const int xcd = id % 8, local = id / 8;
-  return (xcd < r) ? xcd * (q + 1) + local : r * (q + 1) + (xcd - r) * q + local;
-}
 
 }  // namespace t256
 }  // namespace wide

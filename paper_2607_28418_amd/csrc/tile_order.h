@@ -1,0 +1,135 @@
+// Which tile, chunk or place each workgroup of the large kernels takes: index
+// arithmetic only, used by the kernels and by the host code that sizes their
+// launches.  It includes no HIP header, so that a host compiler takes it too
+// (the cover tests run it).
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#if defined(__HIP__)
+#define WIDE_ORDER __host__ __device__ inline __attribute__((always_inline))
+#else
+#define WIDE_ORDER inline
+#endif
+
+namespace wide {
+
+// Workgroup id -> tile id: each XCD (workgroups are dealt round-robin to the
+// 8 XCDs) walks a contiguous range of tile ids.
+WIDE_ORDER int xcd_remap(int id, int n) {
+  const int q = n / 8, r = n % 8;
+  const int xcd = id % 8, local = id / 8;
+  return (xcd < r) ? xcd * (q + 1) + local : r * (q + 1) + (xcd - r) * q + local;
+}
+
+// ---- N axis, m-blocked -----------------------------------------------------------
+// Each XCD takes an eighth of the `cols` column tiles and runs m-tile 0 of each
+// of them, then m-tile 1, and so on; with `halves`, over one half of its columns
+// and then the other (where a half has two groups, of ntpg column tiles, or more).
+// Workgroups per XCD:
+WIDE_ORDER int mblock_share(int cols, int m_tiles) { return (cols + 7) / 8 * m_tiles; }
+// Workgroup `local` of an XCD (m_tile = m_tiles: padding).
+WIDE_ORDER void mblock_place(int cols, int m_tiles, int ntpg, bool halves, int xcd, int local, int& col, int& m_tile) {
+  int c0 = cols * xcd / 8, n = cols * (xcd + 1) / 8 - c0, l = local;
+  if (halves && n >= 4 * ntpg) {
+    const int h = n / 2;
+    if (l < h * m_tiles) {
+      n = h;
+    } else {
+      l -= h * m_tiles;
+      c0 += h;
+      n -= h;
+    }
+  }
+  const int m = n ? l / n : m_tiles;
+  m_tile = m < m_tiles ? m : m_tiles;
+  col = c0 + (n ? l % n : 0);
+}
+
+// ---- K axis, dense-masked (256 x 256 tiles, one workgroup a CU, 256 a round) -------
+constexpr int kKdTile = 256, kKdStep = 64;
+// Up to this many groups the rows go in mask-pattern order.
+constexpr int kPatternMaxGroups = 8;
+
+// Tiles [0, total): full rounds in XCD blocks where the column tiles allow it
+// (round r covers the m-tiles [r mr, (r + 1) mr), mr = 256 / n_tiles, and XCD x
+// a block of mr / 4 m-tiles by n_tiles / 2 column tiles of them), the rest m-major.
+WIDE_ORDER void kd256_coords(int id, int n_tiles, int total, int& m_tile, int& n_tile) {
+  const bool blocks = n_tiles % 2 == 0 && n_tiles <= 256 && 256 % n_tiles == 0 && (256 / n_tiles) % 4 == 0;
+  const int rounds = blocks ? total / 256 : 0;
+  if (id < rounds * 256) {
+    const int xcd = id % 8, local = id / 8;  // workgroups are dealt round-robin to the 8 XCDs
+    const int r = local / 32, q = local % 32;
+    const int mr = 256 / n_tiles, bm = mr / 4, bn = n_tiles / 2;
+    m_tile = r * mr + (xcd % 4) * bm + q % bm;
+    n_tile = (xcd / 4) * bn + q / bm;
+    return;
+  }
+  const int base = rounds * 256;
+  const int tile = base + xcd_remap(id - base, total - base);  // m-major: n-tiles share the A panel
+  m_tile = tile / n_tiles;
+  n_tile = tile % n_tiles;
+}
+
+// The last, partial round: tiles [base, total) are each run by `split`
+// workgroups (1: not split), token rows from m0 on; the chunks' partial sums
+// take split * (M - m0) * N floats, at most `avail`.  As many chunks as fill the
+// 256 CUs once, each at least kKdMinSteps steps deep.
+struct Kd256Tail {
+  int base, split;
+  int64_t m0;
+};
+constexpr int kKdMaxSplit = 16, kKdMinSteps = 4;
+constexpr size_t kKd256PartMaxFloats = (size_t)256 * 256 * 256;  // at most 256 chunks of one tile's sums
+WIDE_ORDER Kd256Tail kd256_tail(int64_t M, int N, int K, int ng, size_t avail) {
+  const int n_tiles = N / kKdTile;
+  const int64_t m_tiles = (M + kKdTile - 1) / kKdTile, total = m_tiles * n_tiles;
+  Kd256Tail t{(int)total, 1, M};
+  if (total == 0 || n_tiles > 256) return t;
+  const int mr = 256 / n_tiles;  // m-tiles of a full round
+  const int64_t mb = m_tiles / mr * mr, rem = total - mb * n_tiles, rows = M - mb * kKdTile;
+  // (rows the mask-pattern order may move between a whole and a split tile
+  // keep one summation order: there only launches of less than a round split)
+  if (rem == 0 || (mb > 0 && ng > 1 && ng <= kPatternMaxGroups)) return t;
+  int64_t split = 256 / rem;
+  if (split > kKdMaxSplit) split = kKdMaxSplit;
+  if (split > K / kKdStep / kKdMinSteps) split = K / kKdStep / kKdMinSteps;
+  if (split > (int64_t)(avail / ((size_t)rows * N))) split = (int64_t)(avail / ((size_t)rows * N));
+  if (split >= 2) t = Kd256Tail{(int)(mb * n_tiles), (int)split, mb * kKdTile};
+  return t;
+}
+// Workgroup tail_base + id: chunk and tile.
+WIDE_ORDER void kd256_chunk(int id, int m_tiles, int n_tiles, int tail_base, int split, int& chunk, int& m_tile,
+                            int& n_tile) {
+  const int rem = m_tiles * n_tiles - tail_base, mt = rem / n_tiles;
+  const int j = xcd_remap(id, rem * split);
+  chunk = j / rem;
+  m_tile = tail_base / n_tiles + j % rem % mt;
+  n_tile = j % rem / mt;
+}
+// The k steps [u0, u1) of chunk c.
+WIDE_ORDER void kd256_steps(int K, int c, int split, int& u0, int& u1) {
+  const int u = K / kKdStep;
+  u0 = u * c / split;
+  u1 = u * (c + 1) / split;
+}
+
+// ---- prefill attention --------------------------------------------------------------
+// Place `rem` of a head block's n_seq * n_slots tiles: `block` sequences at a
+// time, slot by slot from the last (longest key ranges first), the block's
+// sequences in turn.
+WIDE_ORDER void attn_place(int rem, int n_seq, int n_slots, int block, int& slot, int& b) {
+  int b0 = 0, nb = n_seq;
+  if (block < n_seq) {
+    const int per = block * n_slots, i = rem / per;
+    rem -= i * per;
+    b0 = i * block;
+    nb = block < n_seq - b0 ? block : n_seq - b0;
+  }
+  const int up = rem / nb;
+  slot = n_slots - 1 - up;
+  b = b0 + rem - up * nb;
+}
+
+}  // namespace wide
