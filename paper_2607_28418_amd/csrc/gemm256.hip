@@ -143,8 +143,11 @@ __device__ __forceinline__ bool mn256_ordered(const MN256Args& a, const MN256Reg
 // also deals the real tiles in one run: workgroups go round-robin to an
 // XCD's four shader engines, and real and empty tiles in turn (two m-tiles
 // per group, one empty) sent all the real ones to two of them (Llama-7B
-// gate/up, 300 tokens, 64-column tiles: 106 us, now 65).  Launches on
-// 64-column tiles, at most one round, take no halves.
+// gate/up, 300 tokens, 64-column tiles: 106 us, now 65).  The adaptive launch's
+// 64-column tiles, at most one round, take no halves; those of 64-channel groups
+// take them from eight m-tiles on (keep 0.25, 0.5 and 0.75, 14336 channels, 2000
+// tokens: 391, 492 and 615 us without, 355, 464 and 586 with; 4096 tokens 680,
+// 906 and 1127 against 651, 884 and 1111; 500 tokens 178 against 183 at keep 0.5).
 template <int BNO>
 __host__ __device__ __forceinline__ bool mn256_mblocked(const MN256Args& a, const MN256Region& R) {
   return a.mblock && R.masked == kMN256Sorted && (BNO == 64 || R.gw <= (BNO <= 128 ? 512 : 1024));
@@ -157,7 +160,8 @@ __host__ __device__ __forceinline__ int mn256_region_share(const MN256Args& a, c
   return mn256_share(R.tiles);
 }
 
-template <int BNO>
+// FIT: the adaptive launch's narrow tiles, at most one round of real ones.
+template <int BNO, bool FIT = false>
 __device__ __forceinline__ void mn256_coords(const MN256Args& a, const MN256Region& R, int xcd, int local,
                                              int& g, int& m_tile, int& nt_in) {
   const int share = mn256_share(R.tiles);
@@ -166,7 +170,7 @@ __device__ __forceinline__ void mn256_coords(const MN256Args& a, const MN256Regi
   const int per_group = ntpg * a.m_tiles;
   if (mn256_mblocked<BNO>(a, R)) {
     int col;
-    mblock_place(R.tiles / a.m_tiles, a.m_tiles, ntpg, BNO != 64, xcd, local, col, m_tile);
+    mblock_place(R.tiles / a.m_tiles, a.m_tiles, ntpg, !FIT && (BNO != 64 || a.m_tiles >= 8), xcd, local, col, m_tile);
     g = col / ntpg;
     nt_in = col % ntpg;
     return;
@@ -338,7 +342,7 @@ __device__ __forceinline__ void mn256_run(const MN256Args& a, uint16_t* smem) {
   if (DOUBLE) R.tiles *= 2;
   if (!mn256_mblocked<BNO>(a, R) && xcd * mn256_share(R.tiles) + local >= R.tiles) return;  // padding
   int g, nt_in, m_tile;
-  mn256_coords<BNO>(a, R, xcd, local, g, m_tile, nt_in);
+  mn256_coords<BNO, DOUBLE>(a, R, xcd, local, g, m_tile, nt_in);
   if (m_tile >= a.m_tiles) return;  // padding
   const int n0 = g * R.gw + nt_in * BNO;
   const int64_t M = a.M;

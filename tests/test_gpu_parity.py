@@ -603,6 +603,35 @@ def test_qkv_tile_order_edge_counts(orc, M, order):
     check_qkvo(orc, c, kpath=0)
 
 
+@pytest.mark.parametrize("order", [6, 2, 0])
+@pytest.mark.parametrize("M,ng", [(1000, 16), (700, 24), (256, 8), (2000, 36)])
+def test_ffn_half_tile_order_edge_counts(orc, M, ng, order):
+    """The same orders on the half-width tiles of 64-channel groups; 36 groups
+    of eight m-tiles walk an XCD's columns in halves."""
+    say("ffn half tile order", M, ng, order)
+    W.wide_set_option("decode_max_m", 0)
+    W.wide_set_option("mn_order", order)
+    G = 64
+    c = synth.ffn_case(M + ng, M, 256, ng * G, G)
+    c.mask[:] = _edge_count_mask(synth.rng(M * 3 + ng), M, ng)
+    x, wg, wu, wd, m = ffn_dev(c)
+    h = torch.full((M, ng * G), 7.0, dtype=torch.bfloat16, device=dev())
+    y = W.wide_ffn_masked(x, wg, wu, wd, m, G, h_out=h)
+    torch.cuda.synchronize()
+    check_ffn(orc, c, y, h)
+
+
+@pytest.mark.parametrize("order", [0, 1, 2, 3])
+@pytest.mark.parametrize("M", [1000, 300])
+def test_qkv_half_tile_order_edge_counts(orc, M, order):
+    """Q groups of 128 columns, K and V beside them 128 columns wide too."""
+    say("qkv half tile order", M, order)
+    W.wide_set_option("mn_order", order)
+    c = synth.attn_case(M + 17, M, 256, 16, 4, 128, 128, mask="bernoulli")
+    c.mask[:] = _edge_count_mask(synth.rng(M * 5), M, 16)
+    check_qkvo(orc, c, kpath=0)
+
+
 @pytest.mark.parametrize("Dff", [2048, 2112, 6144, 8192, 8704])
 def test_ffn_kd256_group_counts(orc, Dff):
     """The dense-masked K-axis kernel keeps the tile rows' mask words in
