@@ -746,6 +746,20 @@ def test_fp32_tiles(orc, M, D, Dff, G):
     assert torch.equal(y, o)
 
 
+@pytest.mark.parametrize("M,D,n_q,n_kv,hd,G", [
+    (520, 48, 33, 33, 16, 16),    # 17 x 17 tiles of 32: two groups a tile, half tiles at both edges
+    (520, 64, 66, 66, 8, 48),     # groups that start in the middle of a tile
+    (1030, 32, 12, 6, 48, 96),    # K and V narrower than Q
+])
+def test_qkv_fp32_wide_tiles(orc, M, D, n_q, n_kv, hd, G):
+    """Q, K and V in fp32 with 256 tiles of 32 x 32 or more: the plain N axis
+    with two fragments a side, masked and dense."""
+    say("qkv fp32 wide tiles", M, D, n_q, n_kv, hd, G)
+    c = synth.attn_case(M + G, M, D, n_q, n_kv, hd, G, dtype="f32", mask="bernoulli")
+    assert -(-M // 32) * -(-n_kv * hd // 32) >= 256
+    check_qkvo(orc, c, kind="f32")
+
+
 def test_fp32_rows_past_4gib():
     """Sixteen rows of 2^26 floats are 4 GiB: more than a 32-bit byte offset
     reaches.  Factors of -1, 0 and 1 keep every partial sum a whole number
