@@ -142,11 +142,13 @@ wide_status_t wide_ffn_masked(wide_dtype_t dt, int64_t M, int32_t d_model,
  * when h_out is NULL, the K-axis scratch) lives in a device array inside the
  * library of wide_static_scratch_bytes() bytes (32 MiB) per GPU, and the
  * partial sums of the down projection in a second one (64 MiB, enough for any
- * call); both are held until the process ends.  A call needing more scratch
- * than that (wide_workspace_size(WIDE_OP_FFN, ...) > 32 MiB, e.g. a long
- * prefill with h_out NULL) returns WIDE_ERR_WORKSPACE before enqueuing
- * anything.  Nothing is allocated and no library routine that allocates is
- * called.  The first call on a device looks up the array's address on that
+ * call, also per GPU); both belong to every process that loads the library.
+ * A call whose reorder, H and K-axis scratch exceed the first array returns
+ * WIDE_ERR_WORKSPACE before enqueuing anything: in bf16 prefill, roughly 2 M
+ * d_ff bytes of H when h_out is NULL and 4 M d_ff / G of reorder when idx is
+ * (e.g. a long prefill with h_out NULL).  The partial sums that
+ * wide_workspace_size(WIDE_OP_FFN, ...) includes do not count.  Nothing is
+ * allocated and no library routine that allocates is called.  The first call on a device looks up the array's address on that
  * device (make it outside graph capture, with that device current).
  * Every call on one GPU shares that GPU's scratch: calls that overlap on one
  * GPU (concurrent streams, other host threads) race and must be ordered by
@@ -160,7 +162,8 @@ wide_status_t wide_ffn_masked_noalloc(wide_dtype_t dt, int64_t M, int32_t d_mode
                                       const void* w_down, void* h_out, void* y,
                                       hipStream_t stream);
 
-/* Bytes of the per-GPU scratch of wide_ffn_masked_noalloc (32 MiB). */
+/* Bytes of wide_ffn_masked_noalloc's first per-GPU array (32 MiB): the limit of
+ * a call.  Its array of partial sums (64 MiB) is not counted. */
 size_t wide_static_scratch_bytes(void);
 
 /*

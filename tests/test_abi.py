@@ -284,3 +284,14 @@ def test_noalloc_refuses_sizes_beyond_its_scratch_before_any_device_call():
     assert st == W.ERR_WORKSPACE and "static scratch" in err()
     st = L.wide_ffn_masked_noalloc(W.BF16, 8, 4096, 14336, 48, A, None, None, A, A, A, A, None, A, None)
     assert st == W.ERR_INVALID_ARG and "power of two" in err()
+
+
+def test_noalloc_limit_leaves_out_the_partial_sums():
+    """A short prompt's workspace is mostly partial sums of the down projection;
+    those have an array of their own, so the call is not refused for them (a
+    NULL weight, or the missing device, ends it before anything is enqueued)."""
+    L = W.lib()
+    for M in (300, 1000):
+        assert W.wide_workspace_size(W.OP_FFN, W.BF16, M, 4096, 14336, 128) > L.wide_static_scratch_bytes()
+        st = L.wide_ffn_masked_noalloc(W.BF16, M, 4096, 14336, 128, A, None, None, A, None, A, A, None, A, None)
+        assert st in (W.ERR_INVALID_ARG, W.ERR_HIP), err()
