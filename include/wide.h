@@ -124,7 +124,8 @@ wide_status_t wide_mask_reorder(const uint8_t* mask, int64_t M, int32_t n_groups
  *               d_ff, G) bytes.  That size includes up to 64 MiB for partial
  *               sums of the down projection: with less of it the call cuts
  *               fewer tiles along d_ff, or none (slower; the results differ
- *               only in fp32 summation order).
+ *               only in fp32 summation order, which for the rows of the last
+ *               256-row tiles also follows from M).
  */
 wide_status_t wide_ffn_masked(wide_dtype_t dt, int64_t M, int32_t d_model,
                               int32_t d_ff, int32_t group_size,
@@ -308,7 +309,9 @@ wide_status_t wide_attention_masked(wide_dtype_t dt, int64_t n_seq, int32_t T_q,
  *             partial maxima, sums and outputs).
  * Arithmetic: scores from bf16 pairs with fp32 sums; softmax and P.V in fp32
  * (probabilities are not rounded); partial results over key chunks are merged
- * in fp32; o is rounded to bf16.
+ * in fp32; o is rounded to bf16.  Where a sequence's keys are cut, and so the
+ * order of its fp32 sums, follows from the whole batch in large calls (every
+ * sequence's length and active heads); the same call gives the same bits.
  */
 wide_status_t wide_attention_decode(wide_dtype_t dt, int64_t batch, int32_t L, int32_t n_q_heads,
                                     int32_t n_kv_heads, int32_t head_dim, int32_t group_size,

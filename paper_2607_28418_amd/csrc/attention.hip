@@ -109,7 +109,8 @@ __global__ __launch_bounds__(kAT, 2) void wide_attn_fwd(AttnArgs a) {
     // active there is little to skip, and walking many short sequences in turn
     // costs more than it gains (32 of 256 tokens, all active: 72 us sequence
     // by sequence, 88 over all of them), so there they go in blocks of
-    // seq_block (66 us).  Both places' runs are loaded beside the count.
+    // seq_block (66 us); blocks cost sparser groups (24 of 600 at keep 0.25: 86
+    // us over all, 93).  Both places' runs are loaded beside the count.
     attn_place(rem, a.n_seq, a.n_slots, a.n_seq, slot, b);
     s1 = cnt;
     if (a.seq_off) {
@@ -317,8 +318,11 @@ __global__ __launch_bounds__(kAT, 2) void wide_attn_fwd(AttnArgs a) {
   // instructions alternating inside each wave, both units stay busy.  LDS
   // fragments are read three MFMAs ahead of their use.  Everything loaded in
   // one iteration lands before the next one starts.
-  // (Llama-3-8B heads, T = 8192, whole call: keep 0.5 367 -> 362 us, all
-  // active 605 -> 575.)  What is left is the sum of the parts: all active, the
+  // (Whole calls in turn with the two-block form, one sequence, causal, T =
+  // 8192, Llama-3-8B heads: keep 0.25 / 0.5 / 0.75 / 1 208, 332, 449, 575 -> 206,
+  // 328, 444, 567 us; one head a group, keep 0.5 402 -> 391; not causal, 2048 queries
+  // on 4096 keys 139 -> 133; T <= 4096 up to 1%; ranges of one or two key tiles
+  // up to 3% slower with one head a group.)  What is left, all active: the
   // same loop without loads runs 18% faster, without the softmax 14%, without
   // LDS reads 8%, and its MFMAs alone at 1.2 PFLOP/s, held by the chip's power
   // limit.  Measured and not better: two query blocks per wave (half the LDS
@@ -757,6 +761,10 @@ hipError_t launch_attention(AttnArgs a, const uint16_t* v, int32_t* seq_off, hip
     a.split_tiles = 0;
   }
   a.split_rounds = g_attn_split_rounds;
+  // Blocks for groups with most rows active: four sequences where a tile is 32
+  // rows of four heads and the sequences are short (all active, blocks of four
+  // and of eight: 32 x 256 tokens 68 and 75 us, 16 x 512 85 and 91), else eight
+  // (16 x 512 with one head a tile 90 and 90; 8 x 1024 at keep 0.75 101 and 102).
   a.seq_block = hb == 4 && a.T_q < 1024 ? 4 : 8;
   const int n_vt = a.n_seq * a.n_kv * (a.T_kp / 64);
   const int n_off = a.n_seq > 1 ? (a.ng * (a.n_seq + 1) + 3) / 4 : 0;

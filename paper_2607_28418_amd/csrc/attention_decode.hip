@@ -5,14 +5,17 @@
 //
 // One query token per sequence attends to the sequence's cached keys
 // [0, kv_len).  Decode attention is bound by reading the KV cache, so the
-// point of the mask is to read less of it.  A work item is (sequence, KV
-// head, chunk of keys) and packs every query head of that KV head (GQA
-// packing); an item none of whose heads' groups is active for the token
-// returns before touching the cache (l = 0), so an inactive KV head of a
-// token costs no HBM traffic.
+// point of the mask is to read less of it.  The work is cut into segments,
+// runs of keys of one (sequence, KV head) pair, that pack every query head of
+// that KV head (GQA packing); a pair none of whose heads' groups is active for
+// the token is not read (l = 0), so an inactive KV head of a token costs no HBM
+// traffic.  Small calls cut every pair into equal chunks, one wave each, and an
+// inactive pair's waves return at once; large ones list the active units first
+// (the workgroup's waves meet at barriers there) and give every wave an equal
+// run of them, which may cross from one pair into the next (list_units).
 //
-// Each wave is one work item and runs alone (no barriers), streaming its
-// chunk in 16-key units straight into registers with three units in flight
+// Past the listing each wave runs alone, streaming its segments in 16-key units
+// straight into registers with three units in flight
 // (the bytes in flight per CU, not the arithmetic, set the rate here):
 //   scores  S^T[16 keys][16 heads] = K Q^T: four v_mfma_f32_16x16x32_bf16,
 //           K rows as the A operand (16 bytes of a row per lane), the packed
@@ -21,9 +24,9 @@
 //   P.V     on the vector ALUs in fp32: lane = (one of 4 keys of each group
 //           of 4, 8 of the 128 dims); the probabilities and rescale factors
 //           pass through a per-wave LDS scratch.
-// Per (token, head, chunk) the wave leaves (max, sum, unnormalised o) in the
-// workspace; a second kernel merges the chunks (and writes +0 for inactive
-// heads).
+// Per (segment, head) the wave leaves (max, sum, unnormalised o) in the
+// workspace; a second kernel merges a pair's segments (and writes +0 for
+// inactive heads).
 #include <algorithm>
 
 #include "common.h"

@@ -1,18 +1,26 @@
 // Large-tile prefill kernels (256 x 256 tiles, 4 waves, direct-to-LDS loads).
 //
-//   wide_mn256<SWIGLU,BK>  N-axis masked projection (GEMM-MN): gate/up + SwiGLU
-//                          (one tile = 256 sorted tokens x one 128-column slice
-//                          of a group: 128 gate rows + 128 up rows), or plain
-//                          Q/K/V (one tile = 256 tokens x 256 output columns).
-//   wide_kd256<NWR, BK>    K-axis masked projection, dense-masked schedule.
-//   wide_ks256<BK>         K-axis masked projection, scatter schedule (GEMM-K).
+//   wide_mn256       N-axis masked projection (GEMM-MN): gate/up + SwiGLU
+//                    (one tile = 256 sorted tokens x one 128-column slice
+//                    of a group: 128 gate rows + 128 up rows), or plain
+//                    Q/K/V (one tile = 256 tokens x 256 output columns).
+//   wide_mn256_half  the same on half as many columns, for groups that narrow.
+//   wide_mn256_fit   gate/up with few tiles: either width, chosen on the device.
+//   wide_mn256_tail  adds the chunks of the Q/K/V tiles cut along k.
+//   wide_kd256       K-axis masked projection, dense-masked schedule;
+//   wide_kd256_finish  adds the chunks of its tiles cut along k.
+//   wide_ks256       K-axis masked projection, scatter schedule (GEMM-K).
+//
+// Which tile a workgroup takes: tile_order.h, and mn256_coords below for the
+// orders that follow the groups' counts.
 //
 // Semantics, skipping levels and the two K-axis schedules are those of the
 // 128-tile kernels in gemm_mn.hip / gemm_k.hip (WIDE Section 3.1 equations
 // (1)-(3); Section 3.3; Appendix B, Algorithms 2 and 3); only the tile engine
 // differs (tile256.h).  Tiles whose 256 rows are all active take the
 // all-active path (no per-fragment tests), as the paper does for full tiles
-// of a sorted column.  BK is the ring's k depth, 64.
+// of a sorted column.  BK is the ring's k depth, 64; BUF: operands through
+// buffer views.
 #include <algorithm>
 
 #include "common.h"
@@ -425,7 +433,10 @@ __device__ __forceinline__ void mn256_run(const MN256Args& a, uint16_t* smem) {
 
   f32x16 acc[4][NFN];
   zero_acc(acc);
-  int s0 = 0, ns = K / BK;  // a tail chunk runs its share of the k steps
+  // A tail chunk runs its share of the k steps.  (Only Q/K/V launches have any,
+  // but gate/up keeps the test: with s0 a constant the compiler's k loop ran
+  // 10-20% slower.)
+  int s0 = 0, ns = K / BK;
   if (job >= 0) mn256_chunk_steps<BK>(K, chunk, nchunks, s0, ns);
   auto koff = [&](int s) { return (s0 + s) * BK; };
   auto lda = [&](uint16_t* st, int k0, int j) {

@@ -42,7 +42,8 @@ static_assert(2 * (kRT / 8) * kRPad * 4 <= kRNst * 2 * kRTileB, "W2 rows fit in 
 }  // namespace
 
 // RP: bottleneck units carried (16 or 32, at least the rank).  Units past it
-// would only add exact zeros, so both widths give the same bits; at rank 16 the
+// would only add exact zeros, so both widths give the same values (but for the
+// sign of a zero logit, which the mask does not see); at rank 16 the
 // narrow one loads half of W1 and does half of stage 2.
 template <int RP>
 __global__ __launch_bounds__(kRT) void wide_router(RouterArgs a) {
