@@ -27,24 +27,48 @@ WIDE_ORDER int xcd_remap(int id, int n) {
 // Each XCD takes an eighth of the `cols` column tiles and runs m-tile 0 of each
 // of them, then m-tile 1, and so on; with `halves`, over one half of its columns
 // and then the other (where a half has two groups, of ntpg column tiles, or more).
-// Workgroups per XCD:
-WIDE_ORDER int mblock_share(int cols, int m_tiles) { return (cols + 7) / 8 * m_tiles; }
+// The eighths are exact: a column is eight units, XCD x owns units [cols x,
+// cols (x + 1)), and m-tile m of a column goes to the owner of its unit
+// mblock_unit(m), which spreads any run of units over the m-tiles.  (Dealt in
+// whole columns, 108 of them times 7 m-tiles gave four XCDs 98 tiles, two more
+// than three rounds of their 32 CUs.)
+// Bits of m % 8 reversed; bit r of mblock_below(f): unit(r) < f.
+WIDE_ORDER int mblock_unit(int m) { return (m & 1) << 2 | (m & 2) | (m & 4) >> 2; }
+WIDE_ORDER int mblock_below(int f) { return (int)(0x7f77575515110100ull >> (8 * f)) & 0xff; }
+// Tiles of units [u0, u1).
+WIDE_ORDER int mblock_count(int u0, int u1, int m_tiles) {
+  const int r = m_tiles % 8, low = (1 << r) - 1;
+  return m_tiles / 8 * (u1 - u0) + r * (u1 / 8 - u0 / 8) + __builtin_popcount(mblock_below(u1 % 8) & low) -
+         __builtin_popcount(mblock_below(u0 % 8) & low);
+}
+// Workgroups per XCD, at least its tiles:
+WIDE_ORDER int mblock_share(int cols, int m_tiles) { return m_tiles / 8 * cols + m_tiles % 8 * ((cols + 7) / 8); }
 // Workgroup `local` of an XCD (m_tile = m_tiles: padding).
 WIDE_ORDER void mblock_place(int cols, int m_tiles, int ntpg, bool halves, int xcd, int local, int& col, int& m_tile) {
-  int c0 = cols * xcd / 8, n = cols * (xcd + 1) / 8 - c0, l = local;
-  if (halves && n >= 4 * ntpg) {
-    const int h = n / 2;
-    if (l < h * m_tiles) {
-      n = h;
+  int u0 = cols * xcd, u1 = u0 + cols, l = local;
+  if (halves && cols >= 32 * ntpg) {
+    const int mid = (u0 + u1) / 16 * 8, n = mblock_count(u0, mid, m_tiles);
+    if (l < n) {
+      u1 = mid;
     } else {
-      l -= h * m_tiles;
-      c0 += h;
-      n -= h;
+      l -= n;
+      u0 = mid;
     }
   }
-  const int m = n ? l / n : m_tiles;
-  m_tile = m < m_tiles ? m : m_tiles;
-  col = c0 + (n ? l % n : 0);
+  col = 0;
+  m_tile = m_tiles;
+  if (l >= mblock_count(u0, u1, m_tiles)) return;
+  const int below0 = mblock_below(u0 % 8), below1 = mblock_below(u1 % 8);  // m-tiles (mod 8) of the cut columns:
+  const int m8 = l / (u1 - u0), whole = u1 / 8 - u0 / 8;                   // not the first's, also the last's
+  l -= m8 * (u1 - u0);
+  int r = 0, n = whole + (below1 & 1) - (below0 & 1);
+  while (l >= n) {
+    l -= n;
+    ++r;
+    n = whole + (below1 >> r & 1) - (below0 >> r & 1);
+  }
+  col = u0 / 8 + (below0 >> r & 1) + l;
+  m_tile = m8 * 8 + r;
 }
 
 // ---- K axis, dense-masked (256 x 256 tiles, one workgroup a CU, 256 a round) -------

@@ -72,6 +72,15 @@ def test_gate_up_walk_covers_every_tile_once(maps):
             assert all(m == m_tiles for c, m in got if not 0 <= m < m_tiles)
 
 
+def test_gate_up_walk_deals_exact_eighths(maps):
+    """No XCD holds more tiles than its eighth, up to what a column cannot be cut into."""
+    for cols, m_tiles, ntpg in [(108, 7, 2), (86, 13, 1), (4, 33, 4), (43, 5, 1), (112, 32, 1), (54, 3, 2), (1, 40, 1)]:
+        tiles = [0] * 8
+        for i in range(8 * maps.mb_share(cols, m_tiles)):
+            tiles[i % 8] += call(maps.mb_place, 2, cols, m_tiles, ntpg, 1, i)[1] < m_tiles
+        assert max(tiles) <= cols * m_tiles / 8 + 1.5, (cols, m_tiles, tiles)
+
+
 def test_cut_tiles_cover_every_chunk_once_and_fit(maps):
     g = np.random.default_rng(2)
     pattern = maps.pattern_groups()
