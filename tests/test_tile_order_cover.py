@@ -81,6 +81,18 @@ def test_gate_up_walk_deals_exact_eighths(maps):
         assert max(tiles) <= cols * m_tiles / 8 + 1.5, (cols, m_tiles, tiles)
 
 
+def test_gate_up_walk_uses_every_shader_engine(maps):
+    """An XCD's four shader engines take its workgroups in turn.  In rows of an
+    even number of columns (four or more), every other of them empty, the real tiles must not
+    all meet in two of the engines."""
+    for cols, m_tiles in [(64, 9), (96, 13), (128, 6), (160, 21)]:
+        for xcd in range(8):
+            got = [(i, *call(maps.mb_place, 2, cols, m_tiles, 1, 1, 8 * i + xcd))
+                   for i in range(maps.mb_share(cols, m_tiles))]
+            real = np.bincount([i % 4 for i, c, m in got if m < m_tiles and c % 2 == 0], minlength=4)
+            assert real.max() <= 0.375 * real.sum(), (cols, m_tiles, real)
+
+
 def test_cut_tiles_cover_every_chunk_once_and_fit(maps):
     g = np.random.default_rng(2)
     pattern = maps.pattern_groups()
