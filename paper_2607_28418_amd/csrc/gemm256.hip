@@ -634,7 +634,8 @@ __global__ __launch_bounds__(NT) void wide_mn256_tail(MN256Args a) {
 // and a lone tile is bound by one CU's memory latency: about 1.15 us per
 // 64-deep step however few CUs are busy (32 tiles over K = 14336: 250 us).
 // kd256_tail cuts those tiles along k into `split` chunks, one workgroup
-// each, so that they fill the chip once; every chunk writes fp32 partial sums
+// each, in as many chunks as pay for their partial sums, at most one round of
+// workgroups; every chunk writes fp32 partial sums
 // and wide_kd256_finish adds them in chunk order.  Chunks are fixed ranges of
 // k, not shares of the tile's live groups, so a row's sum does not depend on
 // which other rows share its tile.  Workgroups of one chunk and column tile
