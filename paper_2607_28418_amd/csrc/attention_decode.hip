@@ -184,11 +184,14 @@ __global__ __launch_bounds__(kDT, HMAX <= 8 ? 2 : 1) void wide_attn_decode(AttnD
     j_begin = (int)(item % a.n_chunks) * a.chunk;
   }
   for (;; ++p) {  // the wave's segments
+    // Nothing of an inactive pair is loaded: where few heads are active, waves
+    // cross long runs of them.  (An active one follows: units are left.)
+    if (BAL)
+      while (pre(p + 1) == pre(p)) ++p;
     const int b = p / a.n_kv, hkv = p - b * a.n_kv;
     const int len = seq_len(a, b);
     const uint32_t act = active_heads(a, b, hkv);
     if (BAL) {
-      if (pre(p + 1) == pre(p)) continue;  // (an active pair follows: units are left)
       j_end = min(len, (u_end - pre(p)) * kU);
       slot = wave + rank;
     } else {

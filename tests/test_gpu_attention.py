@@ -361,6 +361,33 @@ def test_attention_decode_balanced_split(orc, B, L, n_q, n_kv, G, hm):
                    decode_bound(orc, *args, n_q, n_kv, hd), c.mask[b:b + 1], G, f"decode b={b} len={n}")
 
 
+def test_attention_decode_balanced_split_crosses_inactive_pairs(orc):
+    """As many pairs as the split takes, one in 25 active: a wave's run crosses
+    long runs of pairs of which nothing is read (their cache is NaN)."""
+    say("attention decode balanced, mostly inactive")
+    B, L, hd = 2016, 768, 128
+    g = np.random.default_rng(8)
+    c = synth.attn_decode_case(8, B, 1, 2, 1, hd, 1)
+    mask = (g.random((B, 1)) < 0.04).astype(np.uint8)
+    mask[[0, B - 1]] = [[0], [1]]
+    lens = g.integers(1, L + 1, B).astype(np.int32)
+    gen = torch.Generator(device=dev())
+    gen.manual_seed(8)
+    k, v = (torch.randn(B, L, hd, generator=gen, device=dev()).to(torch.bfloat16) for _ in range(2))
+    off = to_dev(mask)[:, 0] == 0
+    k[off], v[off] = float("nan"), float("nan")
+    o = torch.full((B, 2 * hd), float("nan"), dtype=torch.bfloat16, device=dev())
+    W.wide_attention_decode(to_dev(c.q), k, v, to_dev(mask), 2, 1, hd, 2 * hd, kv_len=to_dev(lens), o=o)
+    torch.cuda.synchronize()
+    got = to_np64(o)
+    assert not got[mask[:, 0] == 0].any() and np.isfinite(got).all()
+    for b in np.flatnonzero(mask[:, 0]):
+        kb, vb = (t[b, :lens[b]].contiguous().view(torch.int16).cpu().numpy().view(np.uint16) for t in (k, v))
+        args = (c.q[b:b + 1], kb, vb, mask[b:b + 1])
+        check_rows(got[b:b + 1], orc.attention(*args, 1, 2, 1, hd, False), decode_bound(orc, *args, 2, 1, hd),
+                   mask[b:b + 1], 2 * hd, f"decode b={b}")
+
+
 def test_attention_decode_balanced_split_by_xcd(orc):
     """Equal lengths of a head-major cache, 16 units a wave: the workgroups'
     runs are dealt XCD by XCD, and each must still be taken once."""
