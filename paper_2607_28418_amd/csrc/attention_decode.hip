@@ -352,7 +352,9 @@ __global__ __launch_bounds__(kDT, HMAX <= 8 ? 2 : 1) void wide_attn_decode(AttnD
 // chunk's weight coming out of its lane by readlane, and four waves' sums
 // meet in LDS.  One wave per head serves few chunks (a barrier costs more than it saves:
 // 2048 heads of one chunk 6.2 us, 7.2 with four); one sequence of 8192 keys (128 chunks a
-// head) takes 15 us with four, and took 39 with one wave and one load at a time.
+// head) takes 15 us with four, and took 39 with one wave and one load at a time.  With more
+// than 2048 heads of short pairs one wave each fills the chip (5312 heads of up to 14 chunks
+// 7.9 us, 13.7 with four).
 template <int WPH>
 __global__ __launch_bounds__(kDT) void wide_attn_decode_merge(AttnDecArgs a) {
   __shared__ float s_o[4][kHd + 1];
@@ -432,11 +434,14 @@ int attn_decode_chunk(int B, int n_kv, int L) {
 // about 16 units (256 keys) per wave on; below, listing the units costs more
 // (2-4 us) than an even split saves: 64 sequences of up to 1000 keys 30 us
 // balanced and 28 in chunks, 32 of up to 4096 (head groups of one head) 59 and
-// 67.  A table of kAttnDecMaxPairs pairs and its segments fit the equal chunks'
-// workspace (at least 4096 partials here).
+// 67.  Short sequences leave a wave several small segments with a start each, and
+// many more waves of equal chunks hide that better: 250 of up to 300 keys 43 us
+// balanced, 36 in chunks, 128 of up to 600 39 and 33; from 900 keys on 4-20% less
+// balanced.  A table of kAttnDecMaxPairs pairs and its segments fit the equal
+// chunks' workspace (at least 4096 partials here).
 int attn_decode_waves(int64_t B, int n_kv, int L) {
   const int64_t pairs = B * n_kv, units = pairs * ((L + kU - 1) / kU);
-  return pairs <= kAttnDecMaxPairs && units >= 32768 && units <= 0x7fffffff ? kAttnDecWaves : 0;
+  return pairs <= kAttnDecMaxPairs && L >= 768 && units >= 32768 && units <= 0x7fffffff ? kAttnDecWaves : 0;
 }
 
 hipError_t launch_attention_decode(AttnDecArgs a, hipStream_t s) {
@@ -458,8 +463,9 @@ hipError_t launch_attention_decode(AttnDecArgs a, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int heads = a.B * a.n_q;
-  const dim3 mg((unsigned)(a.n_chunks > 4 ? heads : (heads + 3) / 4));
-  if (a.n_chunks > 4)
+  const bool wide_merge = a.n_chunks > 4 && (heads <= 2048 || (a.table && a.waves >= 4 * a.B * a.n_kv));
+  const dim3 mg((unsigned)(wide_merge ? heads : (heads + 3) / 4));
+  if (wide_merge)
     WIDE_LAUNCH_NAMED("wide_attn_decode_merge", wide_attn_decode_merge<4>, mg, dim3(kDT), 0, s, a);
   else
     WIDE_LAUNCH_NAMED("wide_attn_decode_merge", wide_attn_decode_merge<1>, mg, dim3(kDT), 0, s, a);

@@ -326,7 +326,7 @@ def test_attention_decode_matches_oracle(orc, B, L, n_q, n_kv, G, ragged, hm):
     (64, 1024, 8, 8, 128, False),      # one head per KV head, at the split's threshold
     (17, 2000, 64, 16, 256, True),     # two groups per KV head
     (40, 1700, 128, 8, 2048, False),   # 16 heads per KV head
-    (2016, 260, 2, 1, 128, False),     # as many pairs as the split takes, waves that cross many of them
+    (2016, 260, 2, 1, 128, False),     # as many pairs as the split takes, too short for it: equal chunks
 ])
 def test_attention_decode_balanced_split(orc, B, L, n_q, n_kv, G, hm):
     """Large calls share the active units evenly over the waves: segments that
