@@ -111,13 +111,13 @@ __global__ __launch_bounds__(kAT, 2) void wide_attn_fwd(AttnArgs a) {
     // by sequence, 88 over all of them), so there they go in blocks of
     // seq_block (66 us); blocks cost sparser groups (24 of 600 at keep 0.25: 86
     // us over all, 93).  Both places' runs are loaded beside the count.
-    attn_place(rem, a.n_seq, a.n_slots, a.n_seq, slot, b);
+    attn_place(rem, a.n_seq, a.n_slots, a.seq_all, slot, b);
     s1 = cnt;
     if (a.seq_off) {
       const int32_t* so = a.seq_off + gg * (a.n_seq + 1);
       s0 = so[b];
       s1 = so[b + 1];
-      if (a.seq_block < a.n_seq) {
+      if (a.seq_block < a.seq_all) {
         int slot_b, bb;
         attn_place(rem, a.n_seq, a.n_slots, a.seq_block, slot_b, bb);
         const int t0 = so[bb], t1 = so[bb + 1];
@@ -766,6 +766,13 @@ hipError_t launch_attention(AttnArgs a, const uint16_t* v, int32_t* seq_off, hip
   // and of eight: 32 x 256 tokens 68 and 75 us, 16 x 512 85 and 91), else eight
   // (16 x 512 with one head a tile 90 and 90; 8 x 1024 at keep 0.75 101 and 102).
   a.seq_block = hb == 4 && a.T_q < 1024 ? 4 : 8;
+  // One, two or four head blocks put a block's tiles on several XCDs, each with
+  // a stretch of them: over all sequences one XCD's stretch is the inactive
+  // tiles, another's the longest ranges, so there the sequences go one by one
+  // (4 heads in one block, 4 x 1750 tokens, keep 0.5: 58 us over all, 54; 16
+  // heads in four, 16 x 437: 49, 39).  Twelve blocks ran up to 30% slower so.
+  const int hblocks = a.n_q / hb;
+  a.seq_all = hblocks < 8 && 8 % hblocks == 0 ? 1 : a.n_seq;
   const int n_vt = a.n_seq * a.n_kv * (a.T_kp / 64);
   const int n_off = a.n_seq > 1 ? (a.ng * (a.n_seq + 1) + 3) / 4 : 0;
   WIDE_LAUNCH(wide_attn_prep, dim3((unsigned)(n_vt + n_off + (a.sched ? 1 : 0))), dim3(kAT), 0, s, a, v, seq_off,

@@ -242,6 +242,7 @@ struct AttnArgs {
   const int32_t* leftpad;   // optional [n_seq]: keys j < leftpad[b] of sequence b are hidden (no split then)
   int split_rounds;         // set by launch_attention
   int seq_block;            // set by launch_attention: sequences whose tiles are dealt together where most rows are active
+  int seq_all;              // set by launch_attention: the same for the other groups (n_seq: all of them)
 };
 // The split: a launch whose active query tiles number at most split_tiles
 // cuts each tile's causal key range into chunks of equal length (at most

@@ -67,10 +67,15 @@ def test_attention_matches_oracle(orc, n_seq, T_q, T_k, n_q, n_kv, G, causal, ma
 @pytest.mark.parametrize("n_seq,T_q,T_k,n_q,n_kv,G,keep", [
     (11, 100, 100, 8, 2, 512, 1.0),    # blocks of four sequences, the last of three
     (9, 70, 130, 4, 4, 128, 0.9),      # blocks of eight, the last of one
-    (11, 100, 100, 8, 2, 512, 0.5),    # mostly inactive: all sequences at once
+    (11, 100, 100, 8, 2, 512, 0.5),    # mostly inactive, two head blocks: sequence by sequence
+    (11, 100, 100, 32, 8, 512, 0.5),   # mostly inactive, eight head blocks: all sequences at once
+    (9, 100, 100, 24, 8, 384, 0.5),    # 24 head blocks
+    (5, 90, 90, 12, 4, 384, 0.9),      # 12 head blocks, all sequences
+    (6, 150, 180, 4, 1, 512, 0.9),     # one head block, most rows active
 ])
 def test_attention_sequences_in_blocks(orc, n_seq, T_q, T_k, n_q, n_kv, G, keep):
-    """Groups with most rows active deal their tiles in blocks of sequences."""
+    """The order of the tiles: all sequences together, in blocks where most rows
+    of a group are active, or one by one where head blocks share XCDs."""
     say("attention blocks", n_seq, T_q, T_k, n_q, n_kv, G, keep)
     run_case(orc, n_seq, T_q, T_k, n_q, n_kv, G, True, mask="bernoulli", keep=keep, seed=n_seq + T_q)
 
