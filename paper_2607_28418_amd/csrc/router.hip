@@ -45,7 +45,9 @@ static_assert(2 * (kRT / 8) * kRPad * 4 <= kRNst * 2 * kRTileB, "W2 rows fit in 
 // would only add exact zeros, so both widths give the same values (but for the
 // sign of a zero logit, which the mask does not see); at rank 16 the
 // narrow one loads half of W1 and does half of stage 2.
-template <int RP>
+// BITS: the reorder's bits are packed (a.bits); calls without a reorder run an
+// instance without that code (3-5% at a few microseconds a call).
+template <int RP, bool BITS>
 __global__ __launch_bounds__(kRT) void wide_router(RouterArgs a) {
   // The ring; after stage 1 the same bytes hold the waves' partials, then
   // stage 2's W2 rows.
@@ -132,10 +134,10 @@ __global__ __launch_bounds__(kRT) void wide_router(RouterArgs a) {
     __syncthreads();
     if (tid < kGPP) s_word[tid] = 0;
   };
-  if (tid < kGPP) s_word[tid] = 0;
+  if (BITS && tid < kGPP) s_word[tid] = 0;
   for (int g0 = 0; g0 < ng; g0 += kGPP) {
     const int gc = min(kGPP, ng - g0);
-    if (a.bits && g0) words(g0 - 1);
+    if (BITS && g0) words(g0 - 1);
     __syncthreads();  // s_h complete; the previous pass is done with s_w2
     {
       const int elems = 2 * gc * r;                 // bf16 values of this pass
@@ -171,24 +173,29 @@ __global__ __launch_bounds__(kRT) void wide_router(RouterArgs a) {
       }
       const int64_t row = t0 + t;
       a.mask[row * ng + g] = r0 >= r1 ? 1 : 0;
-      bits |= (uint32_t)(r0 >= r1) << t;
+      if (BITS) bits |= (uint32_t)(r0 >= r1) << t;
       if (a.logits) {
         a.logits[row * 2 * ng + 2 * g] = r0;
         a.logits[row * 2 * ng + 2 * g + 1] = r1;
       }
     }
-    if (a.bits && bits) atomicOr(&s_word[gl], bits);
+    if (BITS && bits) atomicOr(&s_word[gl], bits);
   }
-  if (a.bits) words(ng - 1);
+  if (BITS) words(ng - 1);
 }
 
 hipError_t launch_router(const RouterArgs& a, hipStream_t s) {
   if (a.M == 0) return hipSuccess;
   const int64_t blocks = (a.M + kRTok - 1) / kRTok;
-  if (a.r <= 16)
-    WIDE_LAUNCH_NAMED("wide_router", wide_router<16>, dim3((unsigned)blocks), dim3(kRT), 0, s, a);
+  const dim3 grid((unsigned)blocks);
+  if (a.r <= 16 && a.bits)
+    WIDE_LAUNCH_NAMED("wide_router", (wide_router<16, true>), grid, dim3(kRT), 0, s, a);
+  else if (a.r <= 16)
+    WIDE_LAUNCH_NAMED("wide_router", (wide_router<16, false>), grid, dim3(kRT), 0, s, a);
+  else if (a.bits)
+    WIDE_LAUNCH_NAMED("wide_router", (wide_router<32, true>), grid, dim3(kRT), 0, s, a);
   else
-    WIDE_LAUNCH_NAMED("wide_router", wide_router<32>, dim3((unsigned)blocks), dim3(kRT), 0, s, a);
+    WIDE_LAUNCH_NAMED("wide_router", (wide_router<32, false>), grid, dim3(kRT), 0, s, a);
   return hipGetLastError();
 }
 
