@@ -180,6 +180,7 @@ __global__ __launch_bounds__(kDT, HMAX <= 8 ? 2 : 1) void wide_attn_decode(AttnD
     // off still leave every XCD the same share of the work.
     const int64_t item = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * 4 + w;
     if (item >= (int64_t)a.B * a.n_kv * a.n_chunks) return;
+    slot = (int)item;
     p = (int)(item / a.n_chunks);
     j_begin = (int)(item % a.n_chunks) * a.chunk;
   }
@@ -196,7 +197,6 @@ __global__ __launch_bounds__(kDT, HMAX <= 8 ? 2 : 1) void wide_attn_decode(AttnD
       slot = wave + rank;
     } else {
       j_end = min(len, j_begin + a.chunk);
-      slot = p * a.n_chunks + j_begin / a.chunk;
       if (act == 0 || j_begin >= j_end) return;  // l = 0: no cache read for this item
     }
 
@@ -371,7 +371,7 @@ __global__ __launch_bounds__(kDT) void wide_attn_decode_merge(AttnDecArgs a) {
   const int p = b * a.n_kv + h / a.qpk;
   const int nc = a.table ? a.table[2 * p + 1] : (len + a.chunk - 1) / a.chunk;
   const int64_t slot = a.table ? a.table[2 * p] : (int64_t)p * a.n_chunks;
-  const int64_t ld = (int64_t)a.qpk * (kHd + 2);  // floats from one chunk's partial to the next
+  const int ld = a.qpk * (kHd + 2);  // floats from one chunk's partial to the next (nc * ld fits 31 bits)
   const float* part = a.part + slot * ld + (h % a.qpk) * (kHd + 2);
   float mx = -INFINITY;
   for (int c0 = 0; c0 < nc; c0 += kWave)
@@ -463,7 +463,8 @@ hipError_t launch_attention_decode(AttnDecArgs a, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int heads = a.B * a.n_q;
-  const bool wide_merge = a.n_chunks > 4 && (heads <= 2048 || (a.table && a.waves >= 4 * a.B * a.n_kv));
+  const bool wide_merge = a.n_chunks > (heads <= 1024 ? 4 : 8) &&
+                          (heads <= 2048 || (a.table && a.waves >= 4 * a.B * a.n_kv));
   const dim3 mg((unsigned)(wide_merge ? heads : (heads + 3) / 4));
   if (wide_merge)
     WIDE_LAUNCH_NAMED("wide_attn_decode_merge", wide_attn_decode_merge<4>, mg, dim3(kDT), 0, s, a);
