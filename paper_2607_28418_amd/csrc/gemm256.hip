@@ -178,7 +178,10 @@ __device__ __forceinline__ void mn256_coords(const MN256Args& a, const MN256Regi
   const int per_group = ntpg * a.m_tiles;
   if (mn256_mblocked<BNO>(a, R)) {
     int col;
-    mblock_place(R.tiles / a.m_tiles, a.m_tiles, ntpg, !FIT && (BNO != 64 || a.m_tiles >= 8), xcd, local, col, m_tile);
+    // (narrow tiles of the adaptive launch, one to a CU, keep their rows in place:
+    // 4096 x 14336, every other group of 512 off, 373 tokens 104 us, shifted 139)
+    mblock_place(R.tiles / a.m_tiles, a.m_tiles, ntpg, !FIT && (BNO != 64 || a.m_tiles >= 8), !FIT, xcd, local, col,
+                 m_tile);
     g = col / ntpg;
     nt_in = col % ntpg;
     return;

@@ -44,7 +44,8 @@ WIDE_ORDER int mblock_count(int u0, int u1, int m_tiles) {
 // Workgroups per XCD, at least its tiles:
 WIDE_ORDER int mblock_share(int cols, int m_tiles) { return m_tiles / 8 * cols + m_tiles % 8 * ((cols + 7) / 8); }
 // Workgroup `local` of an XCD (m_tile = m_tiles: padding).
-WIDE_ORDER void mblock_place(int cols, int m_tiles, int ntpg, bool halves, int xcd, int local, int& col, int& m_tile) {
+WIDE_ORDER void mblock_place(int cols, int m_tiles, int ntpg, bool halves, bool shift, int xcd, int local, int& col,
+                             int& m_tile) {
   int u0 = cols * xcd, u1 = u0 + cols, l = local;
   if (halves && cols >= 32 * ntpg) {
     const int mid = (u0 + u1) / 16 * 8, n = mblock_count(u0, mid, m_tiles);
@@ -67,14 +68,16 @@ WIDE_ORDER void mblock_place(int cols, int m_tiles, int ntpg, bool halves, int x
     ++r;
     n = whole + (below1 >> r & 1) - (below0 >> r & 1);
   }
-  // A row of an even number of columns starts one on in every other m-tile:
-  // workgroups go to an XCD's four shader engines in turn, and with every other
-  // group off the real tiles would else all meet in two of them (4096 x 11008, 953
-  // tokens: 230 us, 160 so; shifts of up to three that follow the engines exactly
-  // gained less there and cost other masks up to 3%).
-  if (r & ~n & 1) l = l + 1 < n ? l + 1 : 0;
-  col = u0 / 8 + (below0 >> r & 1) + l;
   m_tile = m8 * 8 + r;
+  // Workgroups go to an XCD's four shader engines in turn.  In rows of an odd
+  // number of columns a column's m-tiles then meet every engine; with `shift`, rows
+  // of an even number start one column on in every m-tile (every second one where 4
+  // does not divide it), so that theirs do too.  Else, with every other group off
+  // for all tokens, the real tiles would all go to two of the engines (4096 x
+  // 11008, groups of 128, 953 tokens: 235 us, 165 so; 2048 x 8192, groups of 256,
+  // 1500 tokens 151 and 113).
+  if (shift && !(n & 1)) l = (l + (n & 2 ? m_tile >> 1 : m_tile)) % n;
+  col = u0 / 8 + (below0 >> r & 1) + l;
 }
 
 // ---- K axis, dense-masked (256 x 256 tiles, one workgroup a CU, 256 a round) -------

@@ -17,8 +17,8 @@ SHIM = r"""
 using namespace wide;
 extern "C" {
 int mb_share(int cols, int m_tiles) { return mblock_share(cols, m_tiles); }
-void mb_place(int cols, int m_tiles, int ntpg, int halves, int id, int* out) {
-  mblock_place(cols, m_tiles, ntpg, halves != 0, id % 8, id / 8, out[0], out[1]);
+void mb_place(int cols, int m_tiles, int ntpg, int halves, int shift, int id, int* out) {
+  mblock_place(cols, m_tiles, ntpg, halves != 0, shift != 0, id % 8, id / 8, out[0], out[1]);
 }
 void kd_tail(long long M, int N, int K, int ng, unsigned long long avail, long long* out) {
   const Kd256Tail t = kd256_tail(M, N, K, ng, avail);
@@ -66,8 +66,8 @@ def test_gate_up_walk_covers_every_tile_once(maps):
     for cols, m_tiles, ntpg in shapes:
         want = [(c, m) for c in range(cols) for m in range(m_tiles)]
         own = maps.mb_share(cols, m_tiles)
-        for halves, share in ((0, own), (1, own), (0, maps.mb_share(2 * cols, m_tiles))):
-            got = [call(maps.mb_place, 2, cols, m_tiles, ntpg, halves, i) for i in range(8 * share)]
+        for halves, shift, share in ((0, 1, own), (1, 1, own), (0, 0, maps.mb_share(2 * cols, m_tiles))):
+            got = [call(maps.mb_place, 2, cols, m_tiles, ntpg, halves, shift, i) for i in range(8 * share)]
             assert sorted(p for p in got if p[1] < m_tiles) == want, (cols, m_tiles, ntpg, halves)
             assert all(m == m_tiles for c, m in got if not 0 <= m < m_tiles)
 
@@ -77,20 +77,20 @@ def test_gate_up_walk_deals_exact_eighths(maps):
     for cols, m_tiles, ntpg in [(108, 7, 2), (86, 13, 1), (4, 33, 4), (43, 5, 1), (112, 32, 1), (54, 3, 2), (1, 40, 1)]:
         tiles = [0] * 8
         for i in range(8 * maps.mb_share(cols, m_tiles)):
-            tiles[i % 8] += call(maps.mb_place, 2, cols, m_tiles, ntpg, 1, i)[1] < m_tiles
+            tiles[i % 8] += call(maps.mb_place, 2, cols, m_tiles, ntpg, 1, 1, i)[1] < m_tiles
         assert max(tiles) <= cols * m_tiles / 8 + 1.5, (cols, m_tiles, tiles)
 
 
 def test_gate_up_walk_uses_every_shader_engine(maps):
-    """An XCD's four shader engines take its workgroups in turn.  In rows of an
-    even number of columns (four or more), every other of them empty, the real tiles must not
-    all meet in two of the engines."""
-    for cols, m_tiles in [(64, 9), (96, 13), (128, 6), (160, 21)]:
+    """An XCD's four shader engines, eight CUs each, take its workgroups in turn.
+    In rows of an even number of columns, every other group of them empty, the
+    real tiles must not meet in one or two of the engines."""
+    for cols, m_tiles, ntpg in [(64, 9, 1), (96, 13, 1), (128, 16, 1), (48, 33, 2), (64, 13, 2)]:
         for xcd in range(8):
-            got = [(i, *call(maps.mb_place, 2, cols, m_tiles, 1, 1, 8 * i + xcd))
+            got = [(i, *call(maps.mb_place, 2, cols, m_tiles, ntpg, 1, 1, 8 * i + xcd))
                    for i in range(maps.mb_share(cols, m_tiles))]
-            real = np.bincount([i % 4 for i, c, m in got if m < m_tiles and c % 2 == 0], minlength=4)
-            assert real.max() <= 0.375 * real.sum(), (cols, m_tiles, real)
+            real = np.bincount([i % 4 for i, c, m in got if m < m_tiles and c // ntpg % 2 == 0], minlength=4)
+            assert real.max() <= max(8, 0.375 * real.sum()), (cols, m_tiles, real)
 
 
 def test_cut_tiles_cover_every_chunk_once_and_fit(maps):
