@@ -110,7 +110,7 @@ WIDE_ORDER void kd256_coords(int id, int n_tiles, int total, int& m_tile, int& n
 // take split * (M - m0) * N floats, at most `avail`.  At most as many chunks as
 // fill the 256 CUs once, each at least kKdMinSteps steps deep; of that number and
 // the powers of two below it (8 chunks give every XCD one slice of the operands)
-// the one with the least estimated time, if that saves 2 us.
+// the one with the least estimated time, if that saves 1 us.
 struct Kd256Tail {
   int base, split;
   int64_t m0;
@@ -132,7 +132,7 @@ WIDE_ORDER Kd256Tail kd256_tail(int64_t M, int N, int K, int ng, size_t avail) {
   if (split > K / kKdStep / kKdMinSteps) split = K / kKdStep / kKdMinSteps;
   if (split > (int64_t)(avail / ((size_t)rows * N))) split = (int64_t)(avail / ((size_t)rows * N));
   // Measured (K 1024 to 8192, N 1024 to 4096, 200 to 3500 tokens): a whole tile
-  // takes 0.97 us per step, and a cut one its share of that plus 1 us and, for
+  // takes 0.97 us per step, and a cut one its share of that plus 0.5 us and, for
   // the partial sums written and read back, 0.06 us per chunk of 256 rows in the
   // launch.  Cut as often as the CUs allow, calls with little to share lost: K
   // 1024, N 2048, 2000 tokens at keep 0.5 33 us whole, 39 in four; K 1024, N 1024,
@@ -147,9 +147,9 @@ WIDE_ORDER Kd256Tail kd256_tail(int64_t M, int N, int K, int ng, size_t avail) {
     steps *= 1.0f - 0.5f * (float)bits / (float)ng;
   }
   const float chunk_us = 0.06f * (float)(rows * n_tiles) / kKdTile;
-  float best = 0.97f * steps - 2.0f;
+  float best = 0.97f * steps - 1.0f;
   for (int64_t s = 2; s <= split; s = 2 * s <= split || s == split ? 2 * s : split) {
-    const float us = 0.97f * steps / (float)s + 1.0f + chunk_us * (float)s;
+    const float us = 0.97f * steps / (float)s + 0.5f + chunk_us * (float)s;
     if (us < best) {
       best = us;
       t = Kd256Tail{(int)(mb * n_tiles), (int)s, mb * kKdTile};

@@ -128,8 +128,8 @@ def test_cut_tiles_cover_every_chunk_once_and_fit(maps):
 
 @pytest.mark.parametrize("M,N,K,ng,cut", [
     (2000, 2048, 1024, 8, False), (5000, 1024, 1024, 4, False), (1000, 4096, 1024, 4, False),
-    (2000, 4096, 2048, 16, False), (3500, 2048, 2048, 16, False),
-    (200, 1024, 1024, 8, True), (2000, 2048, 2048, 16, True), (777, 4096, 4096, 8, True), (300, 4096, 14336, 112, True),
+    (2000, 4096, 2048, 8, False), (3500, 2048, 2048, 8, False),
+    (1000, 256, 512, 8, True), (200, 1024, 1024, 8, True), (2000, 2048, 2048, 16, True), (777, 4096, 4096, 8, True), (300, 4096, 14336, 112, True),
 ])
 def test_tiles_are_cut_where_it_pays(maps, M, N, K, ng, cut):
     """Measured both ways: few steps to share do not pay for the partial sums."""
